@@ -430,62 +430,19 @@ struct StagedTile {
 // The staged epilogues take the accumulators of either layout of a 128 x
 // 128 tile: J = 2, four waves (wm, wn) of 64 x 64 (2 x 2 blocks, columns
 // 64 wn + 32 j), 256 threads; J = 1, eight waves (wm, wn) of 64 x 32 (rows
-// 64 wm + 32 i, columns 32 wn), 512 threads.
-template <int J> struct EpiThreads { static constexpr int value = J == 2 ? 256 : 512; };
-
-// Bias (+ GELU) in float32, bf16 output.
+// 64 wm + 32 i, columns 32 wn), 512 threads.  They go to LDS as they are;
+// the element-wise part runs on the way out, in one compact loop.
 template <int J>
-__device__ __forceinline__ void epi_bias_staged(const GemmProblem& P, int bt, int m0, int n0,
-                                                f32x16_t (&acc)[2][J], const StagedTile& L, int tid,
-                                                int lane, int wm, int wn) {
-  constexpr int NTH = EpiThreads<J>::value;
-  const int M = P.M, N = P.N;
-  const bf16_t* __restrict__ bias = static_cast<const bf16_t*>(P.bias);
-  const bool gelu = P.epi == EPI_BIAS_GELU;
+__device__ __forceinline__ void stage_acc(const f32x16_t (&acc)[2][J], const StagedTile& L, int lane, int wm, int wn) {
 #pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int cl = wn * (32 * J) + j * 32 + acc_col(lane);
-    const float bv = (bias && n0 + cl < N) ? bf16_to_f32(bias[n0 + cl]) : 0.0f;
+  for (int j = 0; j < J; ++j)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float v = acc[i][j][r] + bv;
-        if (gelu) v = gelu_erf(v);
-        L.row(wm * 64 + i * 32 + acc_row(r, lane))[cl] = v;
-      }
-  }
-  __syncthreads();
-  bf16_t* __restrict__ C = static_cast<bf16_t*>(P.C) + bt * P.strideC;
-  const bool vec = (P.ldc & 7) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
-#pragma unroll 2
-  for (int e = tid; e < BM * (BN / 8); e += NTH) {  // 8 columns per item
-    const int r = e >> 4, c8 = (e & 15) * 8;
-    const int row = m0 + r, col = n0 + c8;
-    if (row >= M || col >= N) continue;
-    const float4 x = *reinterpret_cast<const float4*>(L.row(r) + c8);
-    const float4 y = *reinterpret_cast<const float4*>(L.row(r) + c8 + 4);
-    const float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-    bf16_t* dst = C + (long long)row * P.ldc + col;
-    if (vec && col + 8 <= N) {
-      uint4 o;
-      o.x = f32_to_bf16(f[0]) | (static_cast<uint32_t>(f32_to_bf16(f[1])) << 16);
-      o.y = f32_to_bf16(f[2]) | (static_cast<uint32_t>(f32_to_bf16(f[3])) << 16);
-      o.z = f32_to_bf16(f[4]) | (static_cast<uint32_t>(f32_to_bf16(f[5])) << 16);
-      o.w = f32_to_bf16(f[6]) | (static_cast<uint32_t>(f32_to_bf16(f[7])) << 16);
-      *reinterpret_cast<uint4*>(dst) = o;
-    } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (col + k < N) dst[k] = f32_to_bf16(f[k]);
-    }
-  }
+      for (int r = 0; r < 16; ++r)
+        L.row(wm * 64 + i * 32 + acc_row(r, lane))[wn * (32 * J) + j * 32 + acc_col(lane)] = acc[i][j][r];
 }
 
-// The training step's and the decoder layer's epilogues, staged like the
-// bias epilogue so that every global access moves 16 bytes along a row:
-// EPI_F32 (float32 out), EPI_GELU2 (GELU and GELU' of acc + bias), EPI_MUL
-// and EPI_RESID (acc times, or plus, the bf16 aux entry), bf16 out.
 __device__ __forceinline__ uint4 pack_bf16x8(const float (&f)[8]) {
   uint4 o;
   o.x = f32_to_bf16(f[0]) | (static_cast<uint32_t>(f32_to_bf16(f[1])) << 16);
@@ -495,39 +452,62 @@ __device__ __forceinline__ uint4 pack_bf16x8(const float (&f)[8]) {
   return o;
 }
 
-template <int J>
-__device__ __forceinline__ void epi_direct_staged(const GemmProblem& P, int bt, int m0, int n0,
-                                                  f32x16_t (&acc)[2][J], const StagedTile& L, int tid,
-                                                  int lane, int wm, int wn) {
-  constexpr int NTH = EpiThreads<J>::value;
+// The eight bf16 values at src (16 bytes when `vec`, else n of them, then zeros).
+__device__ __forceinline__ void load_bf16x8(const bf16_t* src, bool vec, int n, float (&a)[8]) {
+  if (vec) {
+    const uint4 u = *reinterpret_cast<const uint4*>(src);
+    const uint32_t w4[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      a[2 * k] = __uint_as_float(w4[k] << 16);
+      a[2 * k + 1] = __uint_as_float(w4[k] & 0xffff0000u);
+    }
+  } else {
+    for (int k = 0; k < 8; ++k) a[k] = k < n ? bf16_to_f32(src[k]) : 0.0f;
+  }
+}
+
+__device__ __forceinline__ void store_bf16x8(bf16_t* dst, bool vec, int n, const float (&f)[8]) {
+  if (vec) {
+    *reinterpret_cast<uint4*>(dst) = pack_bf16x8(f);
+  } else {
+    for (int k = 0; k < n; ++k) dst[k] = f32_to_bf16(f[k]);
+  }
+}
+
+// The row-wise epilogues over a staged tile of 128 rows by W = 128 or 256
+// columns (columns 0..127 in L0, 128.. in L1): bias (+ GELU), float32,
+// GELU and GELU' of acc + bias, acc times or plus the bf16 aux entry; every
+// global access moves 16 bytes along a row.
+template <int W, int NTH>
+__device__ __forceinline__ void store_rows(const GemmProblem& P, int bt, int m0, int n0, const StagedTile& L0,
+                                           const StagedTile& L1, int tid) {
   const int M = P.M, N = P.N, e = P.epi;
   const bf16_t* __restrict__ bias = static_cast<const bf16_t*>(P.bias);
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int cl = wn * (32 * J) + j * 32 + acc_col(lane);
-    const float bv = (e == EPI_GELU2 && bias && n0 + cl < N) ? bf16_to_f32(bias[n0 + cl]) : 0.0f;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) L.row(wm * 64 + i * 32 + acc_row(r, lane))[cl] = acc[i][j][r] + bv;
-  }
-  __syncthreads();
   const long long base = bt * P.strideC;
-  const bool vec = (P.ldc & 7) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15) == 0 &&
-                   (!P.aux || (reinterpret_cast<uintptr_t>(P.aux) & 15) == 0) && (base & 7) == 0;
+  const bool aligned = (P.ldc & 7) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15) == 0 &&
+                       (!P.aux || (reinterpret_cast<uintptr_t>(P.aux) & 15) == 0) && (base & 7) == 0;
+  const bool biased = bias && (e == EPI_BIAS_GELU || e == EPI_BIAS || e == EPI_GELU2);
+  // a thread's items share their columns (NTH is a multiple of W / 8)
+  const int c8 = (tid % (W / 8)) * 8, col = n0 + c8;
+  if (col >= N) return;
+  const int n = min(8, N - col);
+  const bool vec = aligned && n == 8;
+  float bv[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) bv[k] = biased && k < n ? bf16_to_f32(bias[col + k]) : 0.0f;
 #pragma unroll 2
-  for (int it = tid; it < BM * (BN / 8); it += NTH) {  // 8 columns per item
-    const int r = it >> 4, c8 = (it & 15) * 8;
-    const int row = m0 + r, col = n0 + c8;
-    if (row >= M || col >= N) continue;
-    const float4 x = *reinterpret_cast<const float4*>(L.row(r) + c8);
-    const float4 y = *reinterpret_cast<const float4*>(L.row(r) + c8 + 4);
-    float f[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+  for (int r = tid / (W / 8); r < BM; r += NTH / (W / 8)) {
+    const int row = m0 + r;
+    if (row >= M) break;
+    const float* src = W > BN && c8 >= BN ? L1.row(r) + (c8 - BN) : L0.row(r) + c8;
+    const float4 x = *reinterpret_cast<const float4*>(src);
+    const float4 y = *reinterpret_cast<const float4*>(src + 4);
+    float f[8] = {x.x + bv[0], x.y + bv[1], x.z + bv[2], x.w + bv[3], y.x + bv[4], y.y + bv[5], y.z + bv[6], y.w + bv[7]};
     const long long at = base + (long long)row * P.ldc + col;
-    const int n = min(8, N - col);
     if (e == EPI_F32) {
       float* dst = static_cast<float*>(P.C) + at;
-      if (vec && n == 8) {
+      if (vec) {
         reinterpret_cast<float4*>(dst)[0] = x;
         reinterpret_cast<float4*>(dst)[1] = y;
       } else {
@@ -535,46 +515,22 @@ __device__ __forceinline__ void epi_direct_staged(const GemmProblem& P, int bt, 
       }
       continue;
     }
-    bf16_t* dst = static_cast<bf16_t*>(P.C) + at;
     if (e == EPI_GELU2) {
       float g[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        g[k] = gelu_erf_grad(f[k]);
-        f[k] = gelu_erf(f[k]);
-      }
-      bf16_t* dst2 = static_cast<bf16_t*>(P.aux) + at;
-      if (vec && n == 8) {
-        *reinterpret_cast<uint4*>(dst) = pack_bf16x8(f);
-        *reinterpret_cast<uint4*>(dst2) = pack_bf16x8(g);
-      } else {
-        for (int k = 0; k < n; ++k) {
-          dst[k] = f32_to_bf16(f[k]);
-          dst2[k] = f32_to_bf16(g[k]);
-        }
-      }
-      continue;
+      for (int k = 0; k < 8; ++k) g[k] = gelu_erf_grad(f[k]);
+      store_bf16x8(static_cast<bf16_t*>(P.aux) + at, vec, n, g);
     }
-    const bf16_t* src = static_cast<const bf16_t*>(P.aux) + at;  // EPI_MUL, EPI_RESID
-    float a8[8];
-    if (vec && n == 8) {
-      const uint4 u = *reinterpret_cast<const uint4*>(src);
-      const uint32_t w4[4] = {u.x, u.y, u.z, u.w};
+    if (e == EPI_BIAS_GELU || e == EPI_GELU2) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        a8[2 * k] = __uint_as_float(w4[k] << 16);
-        a8[2 * k + 1] = __uint_as_float(w4[k] & 0xffff0000u);
-      }
-    } else {
-      for (int k = 0; k < 8; ++k) a8[k] = k < n ? bf16_to_f32(src[k]) : 0.0f;
-    }
+      for (int k = 0; k < 8; ++k) f[k] = gelu_erf(f[k]);
+    } else if (e == EPI_MUL || e == EPI_RESID) {
+      float a8[8];
+      load_bf16x8(static_cast<const bf16_t*>(P.aux) + at, vec, n, a8);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) f[k] = e == EPI_MUL ? f[k] * a8[k] : f[k] + a8[k];
-    if (vec && n == 8) {
-      *reinterpret_cast<uint4*>(dst) = pack_bf16x8(f);
-    } else {
-      for (int k = 0; k < n; ++k) dst[k] = f32_to_bf16(f[k]);
+      for (int k = 0; k < 8; ++k) f[k] = e == EPI_MUL ? f[k] * a8[k] : f[k] + a8[k];
     }
+    store_bf16x8(static_cast<bf16_t*>(P.C) + at, vec, n, f);
   }
 }
 
@@ -583,15 +539,10 @@ __device__ __forceinline__ void epi_direct_staged(const GemmProblem& P, int bt, 
 // A diagonal tile takes the entries below its diagonal from the transposed
 // copy (the mirror of the entries above it).
 template <int J>
-__device__ __forceinline__ void epi_cosine_staged(const GemmProblem& P, int bt, int tm, int tn,
-                                                  f32x16_t (&acc)[2][J], const StagedTile& L,
-                                                  const float* rs_rows, const float* rs_cols, int tid,
-                                                  int lane, int wm, int wn, bool active = true) {
-  constexpr int NTH = EpiThreads<J>::value;
-  const int M = P.M, N = P.N, m0 = tm * BM, n0 = tn * BN;
-  const bool diag = tm == tn;
+__device__ __forceinline__ void cosine_stage(f32x16_t (&acc)[2][J], const StagedTile& L, const float* rs_rows,
+                                             const float* rs_cols, int lane, int wm, int wn) {
 #pragma unroll
-  for (int j = 0; active && j < J; ++j) {
+  for (int j = 0; j < J; ++j) {
     const int cl = wn * (32 * J) + j * 32 + acc_col(lane);
     const float sc = rs_cols[cl];
 #pragma unroll
@@ -608,8 +559,12 @@ __device__ __forceinline__ void epi_cosine_staged(const GemmProblem& P, int bt, 
         *reinterpret_cast<float4*>(L.col_chunk(cl, rl0 >> 2)) = make_float4(v[0], v[1], v[2], v[3]);
       }
   }
-  __syncthreads();
-  if (!active) return;  // (a workgroup's other half: only the barrier above)
+}
+
+template <int NTH>
+__device__ __forceinline__ void cosine_store(const GemmProblem& P, int bt, int tm, int tn, const StagedTile& L, int tid) {
+  const int M = P.M, N = P.N, m0 = tm * BM, n0 = tn * BN;
+  const bool diag = tm == tn;
   float* __restrict__ S = static_cast<float*>(P.C) + bt * P.strideC;
   const bool vec = (P.ldc & 3) == 0;
   // S[m0 + r][n0 + 4 ch ..]: row r of the tile (the mirror below a diagonal tile's diagonal)
@@ -888,11 +843,14 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
   const StagedTile L{reinterpret_cast<float*>(&st0[0][0][0]), reinterpret_cast<float*>(&st1[0][0][0]),
                      reinterpret_cast<float*>(&st2[0][0][0]), reinterpret_cast<float*>(&st3[0][0][0])};
   if (P.epi == EPI_COSINE)
-    epi_cosine_staged<1>(P, bt, tm, tn, acc, L, rs_tile, rs_tile + BM, tid, lane, wm, wn);
-  else if (P.epi == EPI_BIAS_GELU || P.epi == EPI_BIAS)
-    epi_bias_staged<1>(P, bt, m0, n0, acc, L, tid, lane, wm, wn);
+    cosine_stage<1>(acc, L, rs_tile, rs_tile + BM, lane, wm, wn);
   else
-    epi_direct_staged<1>(P, bt, m0, n0, acc, L, tid, lane, wm, wn);
+    stage_acc<1>(acc, L, lane, wm, wn);
+  __syncthreads();
+  if (P.epi == EPI_COSINE)
+    cosine_store<kDmaThreads>(P, bt, tm, tn, L, tid);
+  else
+    store_rows<BN, kDmaThreads>(P, bt, m0, n0, L, L, tid);
 }
 
 // ------------------------------------------------------------ 256 x 256 tiles
@@ -900,27 +858,58 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
 // images, the decoder layer's long products) run 256 x 256 tiles: per
 // product a compute unit then moves half the bytes from L2 into LDS and
 // reads half as many operand bytes from LDS as with 128 x 128 tiles, which
-// is what bounds the smaller tile.  512 threads, eight wave64s, two per
-// SIMD; wave w (group h = w / 4, (qm, qn) = ((w / 2) % 2, w % 2)) owns rows
-// 128 h + 64 qm + (0..63) and columns 128 s + 64 qn + (0..63) for s = 0, 1,
-// i.e. 2 x 4 MFMA 32x32 blocks whose two A operands serve four products.
-// Group h then holds sub-tiles (h, 0) and (h, 1) in the 128 x 128 kernel's
-// accumulator layout and finishes them with its epilogues, staging through
-// its own 64 KiB; the cosine epilogue (a Gram matrix's upper triangle of
-// tiles, mirrored) needs 128 KiB per sub-tile, so the two groups take turns
-// there, sub-tile by sub-tile, and a diagonal tile's sub-tile below the
-// diagonal is the mirror of the one above it.  Two 64 KiB stages: one K
-// slice loads while the matrix cores consume the other.  Tiles are ordered
-// in groups of kBigRows tile rows, column by column inside a group (a
-// triangular problem: its upper triangle row by row), each XCD taking a
-// contiguous range.
+// is what bounds the smaller tile.  512 threads, eight wave64s, two per SIMD;
+// wave (wm, wn) = (w / 4, w % 4) owns rows 128 i + 64 wm + (0..63) and columns
+// 128 j + 32 wn + (0..31) for i, j = 0, 1: in each of the four 128 x 128
+// sub-tiles (i, j) the layout of the 128 x 128 kernel, whose epilogues finish
+// them one after the other.
+//
+// What bounds the loop: LDS moves 128 bytes per clock, and a 64-wide slice
+// needs 192 KiB of operand reads and 64 KiB of direct-load writes there, 2048
+// clocks, as many as its products take on a SIMD.  Neither may wait for the
+// other, so the waves run in two groups (w / 4), half a phase apart: a SIMD
+// holds one wave of each, and while one group's waves run the eight products
+// of a phase the other group's read the operands of their next phase.  A
+// slice has four phases, one per sub-tile; every phase is [operand reads,
+// one half-tile's direct loads] barrier [products] barrier, and group 1 starts
+// one barrier late.  Half-tiles (A or B, 128 rows by one slice, 16 KiB) sit
+// in two buffers; each is reloaded as soon as both groups have read it, so
+// 7 half-tiles (112 KiB) are in flight or waiting ahead of the reads.
+// Against the former loop (one barrier per slice, all waves in step):
+// 46080 x 1024 x 4096 461 -> 365 us, 8192 x 8192 x 8192 957 -> 808 us (1360
+// TFLOP/s).  On operands that are all zero the latter takes 597 us: what is
+// left is the clock that the power limit leaves.  (Reading every operand one
+// phase ahead, with both halves of A and B in registers, is no faster: 905 us.)
+// Tiles are ordered in groups of kBigRows tile rows, column by column inside
+// a group (a triangular problem: its upper triangle row by row), each XCD
+// taking a contiguous range.
 constexpr int kBig = 256;
 constexpr int kBigThreads = 512;
 constexpr int kBigRows = 4;
 
+// dma16 with a wave-uniform base and a 32-bit byte offset per lane.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // M0 is written here and in dma16 only
+__device__ __forceinline__ void dma16_off(const void* base, uint32_t off, uint32_t m) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0" : : "s"(base), "v"(off), "s"(m) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
+// Barrier that neither the compiler's nor the scheduler's reordering crosses.
+__device__ __forceinline__ void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// NORMS: the launch has row norms to form (args.norm_tiles).
+template <bool NORMS>
 __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch args) {
-  __shared__ uint4 bst0[2 * kBig][8], bst1[2 * kBig][8];  // per stage: A rows, then B rows
-  __shared__ float rs_big[2 * kBig];                       // cosine: 1/norm of the tile's rows, then columns
+  // [buffer][half-tile: A rows 0..127, A rows 128.., B rows 0..127, B rows 128..]
+  __shared__ uint4 half[2][4][BM][8];
+  __shared__ float rs_big[2 * kBig];  // cosine: 1/norm of the tile's rows, then columns
   const int tile = xcd_remap(blockIdx.x, args.total_tiles);
   int pi = 0;
 #pragma unroll
@@ -942,157 +931,230 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
   }
   if (P.run_if && P.run_if[bt] == 0) return;
   const int M = P.M, N = P.N, m0 = tm * kBig, n0 = tn * kBig;
-  const bf16_t* __restrict__ A = static_cast<const bf16_t*>(P.A) + bt * P.strideA;
-  const bf16_t* __restrict__ B = static_cast<const bf16_t*>(P.B) + bt * P.strideB;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int h = wave >> 2, qm = (wave >> 1) & 1, qn = wave & 1;
-  const int nk = P.K / 64;
-  float rs_mine = 0.0f;  // cosine epilogue: 1/norm of tile row tid, or of column tid - 256
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+  const int nk = P.K / 64;  // a multiple of 4 (checked by the host)
+  float rs_mine = 0.0f;     // cosine epilogue: 1/norm of tile row tid, or of column tid - 256
   if (P.epi == EPI_COSINE) {
     const int k = tid < kBig ? m0 + tid : n0 + tid - kBig;
     if (k < (tid < kBig ? M : N)) rs_mine = P.rs[(long long)bt * M + k];
   }
-  // wave w loads rows 32 w .. 32 w + 31 of the A tile and of the B tile,
-  // one instruction per 8 rows (rows past the matrix read its last row)
+  // Wave w loads rows 16 w .. 16 w + 15 of every half-tile, one instruction
+  // per 8 rows (rows past the matrix read its last row): byte offsets from
+  // the tile's first row, or from the matrix with an index map.
   const int32_t* mapA = P.mapA ? P.mapA + bt * P.mapStride : nullptr;
   const int32_t* mapB = P.mapB ? P.mapB + bt * P.mapStride : nullptr;
-  const bf16_t* ga[4];
-  const bf16_t* gb[4];
+  const char* baseA = reinterpret_cast<const char*>(static_cast<const bf16_t*>(P.A) + bt * P.strideA +
+                                                    (mapA ? 0 : (long long)m0 * P.lda));
+  const char* baseB = reinterpret_cast<const char*>(static_cast<const bf16_t*>(P.B) + bt * P.strideB +
+                                                    (mapB ? 0 : (long long)n0 * P.ldb));
+  uint32_t off[4][2];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int r = 32 * wave + 8 * j + (lane >> 3);
-    const int v = (lane & 7) ^ swz(r);
-    const int ra = min(m0 + r, M - 1), rb = min(n0 + r, N - 1);
-    ga[j] = A + (long long)(mapA ? mapA[ra] : ra) * P.lda + 8 * v;
-    gb[j] = B + (long long)(mapB ? mapB[rb] : rb) * P.ldb + 8 * v;
-  }
-  const uint32_t wrow = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(wave)) * 32u * 128u;
-  auto issue = [&](uint4 (*dst)[8], int kt) {
-    const int k0 = kt * 64;
-    const uint32_t m = lds_addr(&dst[0][0]) + wrow;
+  for (int x = 0; x < 2; ++x)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      dma16(ga[j] + k0, m + 1024u * j);
-      dma16(gb[j] + k0, m + kBig * 128u + 1024u * j);
+    for (int j = 0; j < 2; ++j) {
+      const int r = 16 * wave + 8 * j + (lane >> 3);
+      const int v = (lane & 7) ^ swz(r);  // the chunk the swizzle puts at position lane & 7 of row r
+      const int ra = min(128 * x + r, M - 1 - m0), rb = min(128 * x + r, N - 1 - n0);
+      off[x][j] = static_cast<uint32_t>(mapA ? mapA[m0 + ra] : ra) * static_cast<uint32_t>(2 * P.lda) + 16u * v;
+      off[2 + x][j] = static_cast<uint32_t>(mapB ? mapB[n0 + rb] : rb) * static_cast<uint32_t>(2 * P.ldb) + 16u * v;
     }
+  const uint32_t wrow = lds_addr(&half[0][0][0][0]) + static_cast<uint32_t>(wave) * 16u * 128u;
+  auto issue = [&](int kt, int buf, int x) {  // half-tile x of slice kt into buffer buf
+    const char* src = (x < 2 ? baseA : baseB) + 128LL * kt;
+    const uint32_t m = wrow + static_cast<uint32_t>(4 * buf + x) * (BM * 128u);
+    dma16_off(src, off[x][0], m);
+    dma16_off(src, off[x][1], m + 1024u);
   };
-  f32x16_t acc[2][2][2];  // [s][i][j]: rows 128 h + 64 qm + 32 i, columns 128 s + 64 qn + 32 j
+
+  f32x16_t acc[2][2][2][1];  // [i][j][block]: rows 128 i + 64 wm + 32 block, columns 128 j + 32 wn
 #pragma unroll
-  for (int s = 0; s < 2; ++s)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[s][i][j][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) acc[i][j][b][0][r] = 0.0f;
   const int lr = lane & 31, lh = lane >> 5;
-  // Row norms (args.norm_tiles): in the first tile column each wave also
-  // sums the squares of one of the two A operands it reads, the one of rows
-  // 128 h + 64 qm + 32 qn + (0..31) (lane l: row l & 31, the k-half l >> 5 of
-  // every 16), in float32, slice after slice; the two halves are added at
-  // the end.  (The two waves of a (h, qm) pair read the same A operands and
-  // sit on different SIMDs, so each SIMD gets an equal share.)
-  const bool sumsq = args.norm_tiles == pi + 1 && tn == 0;
-  float nacc = 0.0f;
-  // The operands of one step of 16 (two buffers: those of the next step are
-  // read while the products of this one run), and the step's products.
-  bf16x8_t a[2][2], b[2][4];
-  auto read = [&](const uint4 (*st)[8], int s, int buf) {
-    const uint4 (*As)[8] = st;
-    const uint4 (*Bs)[8] = st + kBig;
-    const int v = 2 * s + lh;  // 16-byte chunk: k = 16 s + 8 lh + (0..7)
+  bf16x8_t a[2][4], b0[4], b1[4];  // [block][step of 16]
+  auto read_a = [&](int buf, int i) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int r = 128 * h + 64 * qm + 32 * i + lr;
-      a[buf][i] = __builtin_bit_cast(bf16x8_t, As[r][v ^ swz(r)]);
-    }
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int r = 128 * (c >> 1) + 64 * qn + 32 * (c & 1) + lr;
-      b[buf][c] = __builtin_bit_cast(bf16x8_t, Bs[r][v ^ swz(r)]);
+      for (int s = 0; s < 4; ++s) {
+        const int r = 64 * wm + 32 * b + lr;
+        a[b][s] = __builtin_bit_cast(bf16x8_t, half[buf][i][r][(2 * s + lh) ^ swz(lr)]);
+      }
+  };
+  auto read_b = [&](int buf, int j, bf16x8_t (&b)[4]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int r = 32 * wn + lr;
+      b[s] = __builtin_bit_cast(bf16x8_t, half[buf][2 + j][r][(2 * s + lh) ^ swz(lr)]);
     }
   };
-  auto products = [&](int buf) {
-    __builtin_amdgcn_sched_barrier(0);
+  // Row norms (args.norm_tiles).  Row block (i, b) = rows 128 i + 64 wm +
+  // 32 b + (0..31) of both wm is summed by the tiles of column (2 i + b) mod
+  // min(tiles_n, 4), wave wn taking step wn of 16 of every slice (lane l: row
+  // l & 31, eight of the step's values), in float32, slice after slice; the
+  // eight sums of a row meet at the end.  A wave then has 16 vector
+  // instructions per slice, which fit beside the other group's products.
+  // (With all of it on the first tile column, 64 instructions in half of its
+  // waves, each of its slices took 9 % longer, and with it every round.)
+  const int ncol = NORMS && args.norm_tiles == pi + 1 ? min(P.tiles_n, 4) : 0;
+  bool sq[2][2];
+  float nacc[2][2] = {{0.0f, 0.0f}, {0.0f, 0.0f}};
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        acc[c >> 1][i][c & 1] =
-            __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[buf][i], b[buf][c], acc[c >> 1][i][c & 1], 0, 0, 0);
-    if (sumsq) {  // (vector ALU work under the products)
-      const uint4 u = __builtin_bit_cast(uint4, qn ? a[buf][1] : a[buf][0]);
+    for (int b = 0; b < 2; ++b) sq[i][b] = tn < ncol && (2 * i + b) % ncol == tn;
+  auto squares = [&](int buf, int i) {
+    if constexpr (!NORMS) return;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      if (!sq[i][b]) continue;
+      const uint4 u = half[buf][i][64 * wm + 32 * b + lr][(2 * wn + lh) ^ swz(lr)];
       const uint32_t wv[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         const float x = __uint_as_float((k & 1) ? (wv[k >> 1] & 0xffff0000u) : (wv[k >> 1] << 16));
-        nacc = fmaf(x, x, nacc);
+        nacc[i][b] = fmaf(x, x, nacc[i][b]);
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
   };
-  // Slice kt sits in stage kt % 2.  The wait for slice kt + 1 and the
-  // barrier come before the products of kt's last step, so that the next
-  // slice's first operands are read while those run; the barrier also means
-  // every wave is done reading slice kt, whose stage receives slice kt + 2
-  // at the start of the next step.
-  issue(bst0, 0);
-  wait_vm_lgkm0(0);
-  __builtin_amdgcn_s_barrier();
-  read(bst0, 0, 0);
-  for (int kt = 0; kt < nk; ++kt) {
-    uint4 (*cur)[8] = (kt & 1) ? bst1 : bst0;
-    uint4 (*nxt)[8] = (kt & 1) ? bst0 : bst1;
-    if (kt + 1 < nk) issue(nxt, kt + 1);
-    read(cur, 1, 1);
-    products(0);
-    read(cur, 2, 0);
-    products(1);
-    read(cur, 3, 1);
-    products(0);
-    if (kt + 1 < nk) {
-      wait_vm_lgkm0(0);
-      __builtin_amdgcn_s_barrier();
-      read(nxt, 0, 0);
+  auto products = [&](int i, int j, const bf16x8_t (&b)[4]) {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        acc[i][j][c][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c][s], b[s], acc[i][j][c][0], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  // One slice kt in buffer buf (= kt % 2, a constant in the unrolled body).
+  // Hazards: a half-tile is reloaded one phase or more after the phase that
+  // read it, whose reads both groups have waited for by then (B0 is reloaded
+  // in the very next phase, so its reads are waited for before the first
+  // phase's barrier); the loads of slice kt + 1 are waited for in the last
+  // phase, before the barrier that lets either group read it.
+  auto slice = [&](int kt, int buf) {
+    const bool more1 = kt + 1 < nk, more2 = kt + 2 < nk;
+    read_b(buf, 0, b0);
+    __builtin_amdgcn_sched_barrier(0);
+    read_a(buf, 0);
+    if (more1) issue(kt + 1, buf ^ 1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(8)" ::: "memory");
+    phase_barrier();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    products(0, 0, b0);
+    phase_barrier();
+
+    read_b(buf, 1, b1);
+    if (more2) issue(kt + 2, buf, 2);
+    squares(buf, 0);
+    phase_barrier();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    products(0, 1, b1);
+    phase_barrier();
+
+    read_a(buf, 1);
+    if (more2) issue(kt + 2, buf, 0);
+    phase_barrier();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    products(1, 0, b0);
+    phase_barrier();
+
+    if (more2) {
+      issue(kt + 2, buf, 3);
+      squares(buf, 1);
+      asm volatile("s_waitcnt vmcnt(6)" ::: "memory");  // all but the three half-tiles of slice kt + 2
+    } else {
+      squares(buf, 1);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    products(1);
+    phase_barrier();
+    products(1, 1, b1);
+    phase_barrier();
+  };
+  issue(0, 0, 2);
+  issue(0, 0, 0);
+  issue(0, 0, 3);
+  issue(0, 0, 1);
+  issue(1, 1, 2);
+  issue(1, 1, 0);
+  issue(1, 1, 3);
+  asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+  phase_barrier();
+  if (wm) phase_barrier();  // group 1 runs one barrier behind group 0
+  for (int kt = 0; kt < nk; kt += 2) {
+    slice(kt, 0);
+    slice(kt + 1, 1);
   }
-  if (sumsq) {
-    const float t = nacc + __shfl_xor(nacc, 32);
-    const int row = m0 + 128 * h + 64 * qm + 32 * qn + lr;
-    if (lh == 0 && row < M) {
+  if (!wm) phase_barrier();
+  __syncthreads();  // the buffers are free
+  if (NORMS && tn < ncol) {
+    float* sums = reinterpret_cast<float*>(&half[0][0][0][0]);  // [2 i + b][wm][wn][lh][32]
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (sq[q >> 1][q & 1]) sums[(8 * q + wave) * 64 + lane] = nacc[q >> 1][q & 1];
+    __syncthreads();
+    const int q = tid >> 6, row = 128 * (q >> 1) + 32 * (q & 1) + 64 * (lane >> 5) + lr;  // threads 0..255
+    if (q < 4 && q % ncol == tn && m0 + row < M) {
+      float t = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) t += sums[(8 * q + 4 * (lane >> 5)) * 64 + 32 * k + lr];
       const float n = sqrtf(t);
-      args.norms[row] = n;
-      args.ninv[row] = n > 0.0f ? 1.0f / n : 0.0f;
+      args.norms[m0 + row] = n;
+      args.ninv[m0 + row] = n > 0.0f ? 1.0f / n : 0.0f;
     }
+    __syncthreads();
   }
-  __syncthreads();  // the epilogues reuse the stages: group h stages through bst<h>
+  float* stage0 = reinterpret_cast<float*>(&half[0][0][0][0]);
+  float* stage1 = reinterpret_cast<float*>(&half[1][0][0][0]);
   if (P.epi == EPI_COSINE) {
     rs_big[tid] = rs_mine;
-    const StagedTile LC{reinterpret_cast<float*>(&bst0[0][0]), reinterpret_cast<float*>(&bst0[0][0]) + 64 * BN,
-                        reinterpret_cast<float*>(&bst1[0][0]), reinterpret_cast<float*>(&bst1[0][0]) + 64 * BM};
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const int TM = 2 * tm + hh, TN = 2 * tn + s;  // the sub-tile in 128 x 128 tiles
-        if (TM > TN || TM * BM >= M || TN * BN >= N) continue;  // (uniform over the workgroup)
-        __syncthreads();  // the staging is free (and rs_big written)
-        epi_cosine_staged<2>(P, bt, TM, TN, acc[s], LC, rs_big + 128 * hh, rs_big + kBig + 128 * s,
-                             tid & (NT - 1), lane, qm, qn, h == hh);
-      }
+    const StagedTile LC{stage0, stage0 + 64 * BN, stage1, stage1 + 64 * BM};
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+      const int i = q >> 1, j = q & 1, TM = 2 * tm + i, TN = 2 * tn + j;  // the sub-tile in 128 x 128 tiles
+      // (uniform over the workgroup; a diagonal tile's sub-tile below the
+      // diagonal is the mirror of the one above it)
+      if (TM > TN || TM * BM >= M || TN * BN >= N) continue;
+      __syncthreads();  // the staging is free (and rs_big written)
+      const float *rr = rs_big + 128 * i, *rc = rs_big + kBig + 128 * j;
+      if (q == 0)
+        cosine_stage<1>(acc[0][0], LC, rr, rc, lane, wm, wn);
+      else if (q == 1)
+        cosine_stage<1>(acc[0][1], LC, rr, rc, lane, wm, wn);
+      else if (q == 2)
+        cosine_stage<1>(acc[1][0], LC, rr, rc, lane, wm, wn);
+      else
+        cosine_stage<1>(acc[1][1], LC, rr, rc, lane, wm, wn);
+      __syncthreads();
+      cosine_store<kBigThreads>(P, bt, TM, TN, LC, tid);
+    }
     return;
   }
-  float* stg = reinterpret_cast<float*>(h ? &bst1[0][0] : &bst0[0][0]);
-  const StagedTile L{stg, stg + 64 * BN, nullptr, nullptr};
-  const int t2 = tid & (NT - 1);
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    if (s) __syncthreads();  // the staging is read out before it is written again
-    if (P.epi == EPI_BIAS_GELU || P.epi == EPI_BIAS)
-      epi_bias_staged<2>(P, bt, m0 + 128 * h, n0 + 128 * s, acc[s], L, t2, lane, qm, qn);
-    else
-      epi_direct_staged<2>(P, bt, m0 + 128 * h, n0 + 128 * s, acc[s], L, t2, lane, qm, qn);
+  // 128 rows by 256 columns at a time
+  const StagedTile L0{stage0, stage0 + 64 * BN, nullptr, nullptr}, L1{stage1, stage1 + 64 * BN, nullptr, nullptr};
+#pragma unroll 1
+  for (int i = 0; i < 2; ++i) {
+    if (m0 + 128 * i >= M) break;
+    if (i == 0) {
+      stage_acc<1>(acc[0][0], L0, lane, wm, wn);
+      stage_acc<1>(acc[0][1], L1, lane, wm, wn);
+    } else {
+      __syncthreads();  // the staging is read out
+      stage_acc<1>(acc[1][0], L0, lane, wm, wn);
+      stage_acc<1>(acc[1][1], L1, lane, wm, wn);
+    }
+    __syncthreads();
+    store_rows<kBig, kBigThreads>(P, bt, m0 + 128 * i, n0, L0, L1, tid);
   }
 }
 
@@ -1421,6 +1483,8 @@ static int gemm_cus() {
 // layer's and the decoder layer's shapes).
 static bool big_tiles_pay(const GemmBatch& g) {
   if (g.norm_blocks) return false;
+  for (int i = 0; i < g.count; ++i)  // its loads' 32-bit byte offsets (an index map reaches kSubsetMaxN rows)
+    if (g.p[i].lda > (1 << 17) || g.p[i].ldb > (1 << 17)) return false;
   if (g.norm_tiles > 0 && (g.norm_tiles > g.count || g.p[g.norm_tiles - 1].batch != 1)) return false;
   long long t128 = 0, t256 = 0;
   for (int i = 0; i < g.count; ++i) {
@@ -1471,7 +1535,7 @@ hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipSt
     if (dma && big_tiles_pay(g)) {
       GemmBatch q = g;
       finalize_big(q);
-      return launch_kernel(name, gemm_big_kernel, dim3(q.total_tiles), dim3(kBigThreads), 0, s, q);
+      return launch_kernel(name, g.norm_tiles ? gemm_big_kernel<true> : gemm_big_kernel<false>, dim3(q.total_tiles), dim3(kBigThreads), 0, s, q);
     }
     if (dma)
       return launch_kernel(name, gemm_dma_kernel, dim3(g.total_tiles + g.norm_blocks), dim3(kDmaThreads), 0, s, g);
