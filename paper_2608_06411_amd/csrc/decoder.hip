@@ -12,8 +12,8 @@
 // the kernels between them:
 //   rmsnorm     one workgroup per row, 16-byte pieces, float32 sum of squares
 //   rope_qkv    rotates q and k in place, angles pos * theta^(-2i/d_h) in float64
-//   attention   one workgroup per (64 query rows, head, sequence): the key
-//               blocks up to the diagonal through LDS on the bf16 matrix
+//   attention   one workgroup per (64 or 128 query rows, head, sequence): the
+//               key blocks up to the diagonal through LDS on the bf16 matrix
 //               cores with an online softmax; the causal mask follows the
 //               rows' order in their sequence
 //   silu_mul    SiLU(gate) * up, 8 entries per thread
@@ -98,174 +98,197 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 // matrix-core block.
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 
-// LDS strides of the attention tiles (bf16 entries; float32 for the scores).
-constexpr int LQ = DH + 8;   // q and k rows: [64][LQ]
-constexpr int LV = 64 + 8;   // v transposed (dims x keys) and p (queries x keys)
-constexpr int LS = 64 + 4;   // scores [64][LS] float32
-constexpr int kAttnLds = 2 * (2 * 64 * LQ + DH * LV + 64 * LV) + 4 * (64 * LS + 3 * 64);  // q, k, v^T, p; s, stats
+// One global_load_lds_dwordx4: lane l's 16 bytes at gsrc land at byte 16 l of
+// the wave's 1 KiB at LDS address m (wave-uniform).  The wait before each
+// block's barrier covers it.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // M0 is written here and nowhere else in the file
+__device__ __forceinline__ void dma16(const void* gsrc, uint32_t m) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(gsrc), "s"(m) : "memory", "m0");
+}
+#pragma clang diagnostic pop
 
-// Workgroup (query block qb of 64 rows, head h, sequence b), flash-style on
-// the bf16 matrix cores (32 x 32 x 16, float32 accumulation).  For each key
-// block up to the diagonal: wave w forms the 32 x 32 score tile (rows
-// 32 (w / 2), keys 32 (w % 2)) and stores it, scaled and masked, to LDS;
-// four threads per row then take the row's maximum and sum over the block
-// (two quad exchanges) and write p (bf16) and the running statistics; wave
-// w rescales its output tiles (rows 32 (w / 2), dims 64 (w % 2) + 0 and
-// + 32) and adds p v.
-__global__ __launch_bounds__(NT) void attention_kernel(const DecoderArgs a) {
-  extern __shared__ uint4 lds4[];
-  bf16_t* Qs = reinterpret_cast<bf16_t*>(lds4);
-  bf16_t* Ks = Qs + 64 * LQ;
-  bf16_t* VT = Ks + 64 * LQ;
-  bf16_t* Ps = VT + DH * LV;
-  float* Ss = reinterpret_cast<float*>(Ps + 64 * LV);  // [64][LS]
-  float* mrow = Ss + 64 * LS;                           // [64] running maximum
-  float* lrow = mrow + 64;                              // [64] running sum
-  float* alph = lrow + 64;                              // [64] this block's rescaling
-  const int qb = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int s0 = a.seq_off[b], S = a.seq_off[b + 1] - s0, q0 = qb * 64;
+// Causal attention, flash-style on the bf16 matrix cores (32 x 32 x 16,
+// float32 accumulation).  Workgroup (query block of 32 NW rows, head h,
+// sequence b); wave w owns 32 query rows and their softmax.  Both products
+// are formed transposed, S^T = K Q^T and O^T = V^T P^T, so that a lane holds
+// one query (column lane & 31) throughout: the row maximum and sum are sums
+// over its own registers and one exchange with lane ^ 32, the running
+// statistics and the rescaling are per lane, and the scores become the
+// second product's operand in place (its keys are taken in the order in
+// which the lane holds them; V^T is stored in that order).  Nothing but K and V
+// passes through LDS: 64 keys at a time, two buffers, one barrier per block,
+// the next block's loads under this block's products.  Output rows are
+// rescaled only when a row's maximum has grown by more than 2^6 (the sums
+// carry the same factor, so the result is the same softmax).
+// What bounds it: each block's 32 products of a wave (1024 clocks) and the
+// about as long vector work of its softmax, on two waves per SIMD.  The
+// scores took a trip through LDS and five barriers per block before:
+// 2944 rows, 32 heads: 332 us, now 137; 224 rows: 20 us, now 12.
+constexpr int kKeys = 64;              // keys per block
+constexpr int kKBytes = kKeys * DH * 2;  // one buffer of K, and of V^T
+constexpr float kRescale = 6.0f;       // log2 of the growth that a row's factor may lag behind
+
+// 16-byte chunk c of K row r sits at position c ^ (r & 15) of the row's 16;
+// chunk c of V^T row (dim) r at c ^ vswz(r) of its 8.
+__device__ __forceinline__ int vswz(int r) { return ((r >> 1) ^ (r >> 4)) & 7; }
+
+template <int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attention_kernel(const DecoderArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint4 lds[4 * kKBytes / 16];  // K, K, V^T, V^T
+  constexpr int NTH = 64 * NW;
+  constexpr int KI = 16 / NW;                // K: instructions of 4 rows per wave
+  constexpr int VI = 32 * 16 / NTH;          // V: (pair of keys, 8 dims) items per thread
+  const int h = blockIdx.y, b = blockIdx.z;
+  const int s0 = a.seq_off[b], S = a.seq_off[b + 1] - s0;
+  const int q0 = (gridDim.x - 1 - blockIdx.x) * 32 * NW;  // the longest first
   if (q0 >= S) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wi = wave >> 1, wj = wave & 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lh = lane >> 5;
   const long long ld = 3LL * a.d;
-  const bf16_t* qkv = static_cast<const bf16_t*>(a.qkv);
+  const bf16_t* qkv = static_cast<const bf16_t*>(a.qkv) + s0 * ld + h * DH;
+  const int nblk = (min(q0 + 32 * NW, S) + kKeys - 1) / kKeys;
+  const int qw = q0 + 32 * wave, mine = qw < S ? (min(qw + 31, S - 1)) / kKeys + 1 : 0;  // this wave's blocks
+  const int q = qw + lr;  // this lane's query
+
+  bf16x8_t qf[8];  // the query's values 16 st + 8 lh + (0..7)
+  {
+    const bf16_t* row = qkv + min(q, S - 1) * ld + 8 * lh;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {  // the query block, row-major
-    const int e = tid + u * NT, r = e >> 4, c = (e & 15) * 8;
-    *reinterpret_cast<uint4*>(Qs + r * LQ + c) =
-        q0 + r < S ? *reinterpret_cast<const uint4*>(qkv + (s0 + q0 + r) * ld + h * DH + c) : make_uint4(0u, 0u, 0u, 0u);
+    for (int st = 0; st < 8; ++st) qf[st] = *reinterpret_cast<const bf16x8_t*>(row + 16 * st);
   }
-  if (tid < 64) {
-    mrow[tid] = -INFINITY;
-    lrow[tid] = 0.0f;
+  const uint32_t k_lds = static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)&lds[0]));
+  auto load_k = [&](int kb) {  // rows past the sequence read its last row (masked below)
+#pragma unroll
+    for (int u = 0; u < KI; ++u) {
+      const int r = 4 * (wave * KI + u) + (lane >> 4), c = (lane & 15) ^ (r & 15);
+      dma16(qkv + min(kb * kKeys + r, S - 1) * ld + a.d + 8 * c,
+            k_lds + static_cast<uint32_t>(kb & 1) * kKBytes + 1024u * (wave * KI + u));
+    }
+  };
+  Bf8 va[VI], vb[VI];
+  auto load_v = [&](int kb) {
+#pragma unroll
+    for (int u = 0; u < VI; ++u) {
+      const int e = tid + NTH * u, c = e & 15, j = e >> 4;
+      const int k = kb * kKeys + 2 * j;
+      va[u].u = *reinterpret_cast<const uint4*>(qkv + min(k, S - 1) * ld + 2 * a.d + 8 * c);
+      vb[u].u = *reinterpret_cast<const uint4*>(qkv + min(k + 1, S - 1) * ld + 2 * a.d + 8 * c);
+    }
+  };
+  // V^T[dim][position]: key k of a block sits at position k with bits 2 and
+  // 3 exchanged (within every 16: keys 0-3, 8-11, 4-7, 12-15)
+  auto store_v = [&](int kb) {
+    char* vt = reinterpret_cast<char*>(lds) + (2 + (kb & 1)) * kKBytes;
+#pragma unroll
+    for (int u = 0; u < VI; ++u) {
+      const int e = tid + NTH * u, c = e & 15, k = 2 * (e >> 4);
+      const int pos = (k & ~12) | ((k & 4) << 1) | ((k & 8) >> 1);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int dim = 8 * c + i;
+        *reinterpret_cast<uint32_t*>(vt + dim * (2 * kKeys) + 16 * ((pos >> 3) ^ vswz(dim)) + 2 * (pos & 7)) =
+            static_cast<uint32_t>(va[u].e[i]) | (static_cast<uint32_t>(vb[u].e[i]) << 16);
+      }
+    }
+  };
+
+  f32x16_t o[4];  // O^T: rows 32 d4 + acc_row = dims, column lr = the query
+#pragma unroll
+  for (int d4 = 0; d4 < 4; ++d4)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[d4][r] = 0.0f;
+  const float c2 = 1.4426950408889634f / sqrtf(static_cast<float>(DH));  // log2(e) / sqrt(d_h)
+  float m = -INFINITY, l = 0.0f;  // the row's factor 2^-m (both halves agree) and this half's sum
+
+  load_k(0);
+  load_v(0);
+  for (int kb = 0; kb < nblk; ++kb) {
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's part of K; V below
+    store_v(kb);
+    __syncthreads();
+    if (kb + 1 < nblk) {
+      load_k(kb + 1);
+      load_v(kb + 1);
+    }
+    if (kb >= mine) continue;  // (uniform over the wave; it still loads for the others)
+    const uint4* K4 = lds + (kb & 1) * (kKBytes / 16);
+    const uint4* V4 = lds + (2 + (kb & 1)) * (kKBytes / 16);
+    f32x16_t sc[2];  // S^T: rows = keys 32 t + acc_row, column = the query
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sc[t][r] = 0.0f;
+#pragma unroll
+    for (int st = 0; st < 8; ++st)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int row = 32 * t + lr;
+        sc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            __builtin_bit_cast(bf16x8_t, K4[row * 16 + ((2 * st + lh) ^ (row & 15))]), qf[st], sc[t], 0, 0, 0);
+      }
+    if (kb * kKeys + kKeys - 1 > qw) {  // the diagonal
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (kb * kKeys + 32 * t + acc_row(r, lane) > q) sc[t][r] = -INFINITY;
+    }
+    float mx = sc[0][0];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[t][r]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
+    if (__any(mx > m + kRescale)) {
+      const float mn = fmaxf(m, mx), al = __builtin_amdgcn_exp2f(m - mn);  // (first block: 2^-inf = 0)
+      m = mn;
+      l *= al;
+#pragma unroll
+      for (int d4 = 0; d4 < 4; ++d4)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[d4][r] *= al;
+    }
+    bf16x8_t pf[4];  // the probabilities of steps of 16 keys
+#pragma unroll
+    for (int st = 0; st < 4; ++st)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float pv = __builtin_amdgcn_exp2f(fmaf(sc[st >> 1][8 * (st & 1) + k], c2, -m));
+        l += pv;
+        pf[st][k] = static_cast<__bf16>(pv);
+      }
+#pragma unroll
+    for (int st = 0; st < 4; ++st)
+#pragma unroll
+      for (int d4 = 0; d4 < 4; ++d4) {
+        const int row = 32 * d4 + lr;
+        o[d4] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            __builtin_bit_cast(bf16x8_t, V4[row * 8 + ((2 * st + lh) ^ vswz(row))]), pf[st], o[d4], 0, 0, 0);
+      }
   }
-  const float scale = 1.0f / sqrtf(static_cast<float>(DH));
-  f32x16_t o[2];
+  __syncthreads();  // K and V are read out: each wave's output rows through LDS, 128 + 8 values apart
+  if (mine == 0) return;
+  const float inv = 1.0f / (l + __shfl_xor(l, 32, 64));
+  bf16_t* ot = reinterpret_cast<bf16_t*>(lds) + wave * 32 * (DH + 8);
 #pragma unroll
-  for (int jj = 0; jj < 2; ++jj)
+  for (int d4 = 0; d4 < 4; ++d4)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) o[jj][r] = 0.0f;
-  const int srow = tid >> 2, sq = tid & 3;  // the row phase: row, quarter of its 64 keys
-  for (int kb = 0; kb <= qb; ++kb) {
-    const int k0 = kb * 64;
-    __syncthreads();  // the previous block's k, v and p are no longer read
-    // keys row-major (16 rows x 16 pieces per pass); values transposed, a
-    // lane per pair of key rows so that each LDS store is one 32-bit word
-    uint4 kv[4], va[2], vb[2];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + u * NT, r = e >> 4, c = (e & 15) * 8;
-      kv[u] = k0 + r < S ? *reinterpret_cast<const uint4*>(qkv + (s0 + k0 + r) * ld + a.d + h * DH + c)
-                         : make_uint4(0u, 0u, 0u, 0u);
+    for (int g = 0; g < 4; ++g) {
+      ushort4 w;
+      w.x = f32_to_bf16(o[d4][4 * g] * inv);
+      w.y = f32_to_bf16(o[d4][4 * g + 1] * inv);
+      w.z = f32_to_bf16(o[d4][4 * g + 2] * inv);
+      w.w = f32_to_bf16(o[d4][4 * g + 3] * inv);
+      *reinterpret_cast<ushort4*>(ot + lr * (DH + 8) + 32 * d4 + 8 * g + 4 * lh) = w;
     }
+  bf16_t* out = static_cast<bf16_t*>(a.o) + (long long)(s0 + qw) * a.d + h * DH;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int e = tid + u * NT, j = e & 31, c = (e >> 5) * 8, r = 2 * j;
-      va[u] = k0 + r < S ? *reinterpret_cast<const uint4*>(qkv + (s0 + k0 + r) * ld + 2 * a.d + h * DH + c)
-                         : make_uint4(0u, 0u, 0u, 0u);
-      vb[u] = k0 + r + 1 < S ? *reinterpret_cast<const uint4*>(qkv + (s0 + k0 + r + 1) * ld + 2 * a.d + h * DH + c)
-                             : make_uint4(0u, 0u, 0u, 0u);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + u * NT, r = e >> 4, c = (e & 15) * 8;
-      *reinterpret_cast<uint4*>(Ks + r * LQ + c) = kv[u];
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int e = tid + u * NT, j = e & 31, c = (e >> 5) * 8;
-      Bf8 x, y;
-      x.u = va[u];
-      y.u = vb[u];
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        *reinterpret_cast<uint32_t*>(VT + (c + k) * LV + 2 * j) =
-            static_cast<uint32_t>(x.e[k]) | (static_cast<uint32_t>(y.e[k]) << 16);
-    }
-    __syncthreads();
-    // the score tile: rows 32 wi + lr (queries), columns 32 wj + lr (keys)
-    f32x16_t sc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sc[r] = 0.0f;
-#pragma unroll
-    for (int st = 0; st < DH / 16; ++st) {
-      const bf16x8_t qa = *reinterpret_cast<const bf16x8_t*>(Qs + (32 * wi + lr) * LQ + 16 * st + 8 * lh);
-      const bf16x8_t kk = *reinterpret_cast<const bf16x8_t*>(Ks + (32 * wj + lr) * LQ + 16 * st + 8 * lh);
-      sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kk, sc, 0, 0, 0);
-    }
-    {
-      const int col = 32 * wj + lr, kj = k0 + col;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 32 * wi + acc_row(r, lane);
-        Ss[row * LS + col] = (kj <= q0 + row && kj < S) ? sc[r] * scale : -INFINITY;
-      }
-    }
-    __syncthreads();
-    {  // row srow, keys 16 sq .. 16 sq + 15
-      float v[16];
-#pragma unroll
-      for (int k = 0; k < 16; k += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(Ss + srow * LS + 16 * sq + k);
-        v[k] = x.x;
-        v[k + 1] = x.y;
-        v[k + 2] = x.z;
-        v[k + 3] = x.w;
-      }
-      float mx = v[0];
-#pragma unroll
-      for (int k = 1; k < 16; ++k) mx = fmaxf(mx, v[k]);
-      mx = fmaxf(mx, __shfl_xor(mx, 1, 4));
-      mx = fmaxf(mx, __shfl_xor(mx, 2, 4));
-      const float mo = mrow[srow], mn = fmaxf(mo, mx);
-      float sum = 0.0f;
-      Bf8 p0, p1;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const float pv = mn == -INFINITY ? 0.0f : __expf(v[k] - mn);
-        sum += pv;
-        if (k < 8) p0.e[k] = f32_to_bf16(pv);
-        else p1.e[k - 8] = f32_to_bf16(pv);
-      }
-      *reinterpret_cast<uint4*>(Ps + srow * LV + 16 * sq) = p0.u;
-      *reinterpret_cast<uint4*>(Ps + srow * LV + 16 * sq + 8) = p1.u;
-      sum += __shfl_xor(sum, 1, 4);
-      sum += __shfl_xor(sum, 2, 4);
-      __syncthreads();  // every quarter has read mrow before it changes
-      if (sq == 0) {
-        const float al = mn == -INFINITY ? 1.0f : (mo == -INFINITY ? 0.0f : __expf(mo - mn));
-        lrow[srow] = lrow[srow] * al + sum;
-        mrow[srow] = mn;
-        alph[srow] = al;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float al = alph[32 * wi + acc_row(r, lane)];
-      o[0][r] *= al;
-      o[1][r] *= al;
-    }
-#pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      const bf16x8_t pa = *reinterpret_cast<const bf16x8_t*>(Ps + (32 * wi + lr) * LV + 16 * st + 8 * lh);
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const bf16x8_t vb2 = *reinterpret_cast<const bf16x8_t*>(VT + (64 * wj + 32 * jj + lr) * LV + 16 * st + 8 * lh);
-        o[jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa, vb2, o[jj], 0, 0, 0);
-      }
-    }
+  for (int u = 0; u < 8; ++u) {  // (this wave's own rows: no barrier)
+    const int r = 4 * u + (lane >> 4), c = 8 * (lane & 15);
+    if (qw + r < S) *reinterpret_cast<uint4*>(out + (long long)r * a.d + c) = *reinterpret_cast<const uint4*>(ot + r * (DH + 8) + c);
   }
-  __syncthreads();
-  bf16_t* out = static_cast<bf16_t*>(a.o);
-#pragma unroll
-  for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = 32 * wi + acc_row(r, lane);
-      if (q0 + row < S)
-        out[(long long)(s0 + q0 + row) * a.d + h * DH + 64 * wj + 32 * jj + lr] = f32_to_bf16(o[jj][r] / lrow[row]);
-    }
 }
 
 // act[r][i] = SiLU(gu[r][i]) * gu[r][ff + i], 8 entries per thread.
@@ -297,12 +320,13 @@ hipError_t launch_rope_qkv(const DecoderArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_attention(const DecoderArgs& a, hipStream_t s) {
-  constexpr int bytes = kAttnLds;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attention_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e != hipSuccess) return e;
-  return launch_kernel("attention", attention_kernel, dim3((a.max_len + 63) / 64, a.n_heads, a.B), dim3(NT), bytes,
-                       s, a);
+  // 128 query rows per workgroup share each block of K and V; with fewer of
+  // them than two per compute unit, 64 rows, so that more units work.
+  const long long wide = (long long)((a.max_len + 127) / 128) * a.n_heads * a.B;
+  if (wide >= 512)
+    return launch_kernel("attention", attention_kernel<4>, dim3((a.max_len + 127) / 128, a.n_heads, a.B), dim3(256), 0,
+                         s, a);
+  return launch_kernel("attention", attention_kernel<2>, dim3((a.max_len + 63) / 64, a.n_heads, a.B), dim3(128), 0, s, a);
 }
 
 hipError_t launch_silu_mul(const DecoderArgs& a, hipStream_t s) {

@@ -110,3 +110,27 @@ def test_decoder_on_the_pruned_layer0_input():
     seq_off = [b * cfg.K + int(x["t_off"][b]) for b in range(cfg.B + 1)]
     X_bits = f["X"].view(torch.int16).cpu().numpy().view(np.uint16)
     _run_and_check(X_bits, f["pos_x"].cpu().numpy(), seq_off, _weights(512, 768, 7, std=0.04), 4, "layer-0 input")
+
+
+@pytest.mark.parametrize("lens", [
+    [1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 200],        # 64 query rows per workgroup
+    [500, 129, 128, 127, 1, 65, 64, 33, 32, 31] + [97] * 54,  # enough of them for 128 rows each
+])
+def test_decoder_attention_block_edges(lens):
+    """Sequences that end at and beside the edges of the attention's query
+    rows (32 per wave) and key blocks (64), every row of the update held to
+    the update's bar (a row lost or wrongly masked moves its own update by
+    far more)."""
+    d, H, ff = 256, 2, 256
+    announce(f"decoder attention edges, {len(lens)} sequences")
+    rng = np.random.default_rng(len(lens))
+    seq_off = [0] + [int(v) for v in np.cumsum(lens)]
+    R = seq_off[-1]
+    X = f32_to_bf16_bits(rng.standard_normal((R, d)).astype(np.float32))
+    pos = np.concatenate([np.sort(rng.choice(3000, n, replace=False)) for n in lens]).astype(np.int32)
+    wb = _weights(d, ff, 11, std=0.06)
+    got = _run_and_check(X, pos, seq_off, wb, H, "attention edges")
+    x = bf16_bits_to_f32(X).astype(np.float64)
+    want = oracle.decoder_layer(x, pos, seq_off, {k: bf16_bits_to_f32(v) for k, v in wb.items()}, H)
+    row = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want - x, axis=1)
+    assert row.max() <= 3e-2, (int(row.argmax()), float(row.max()))
