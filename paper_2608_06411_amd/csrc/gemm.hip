@@ -144,9 +144,8 @@ __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 
 __device__ __forceinline__ int acc_col(int lane) { return lane & 31; }
 
 // Workgroup -> (problem, batch item, tile row, tile column).
-// The tiles of the problems before args.first_tiles run first, each class
-// XCD-contiguous: the launch puts the layer-1 and fold tiles there, so the
-// second wave of workgroups holds only Gram tiles, whose epilogue is shorter.
+// The tiles before args.first_tiles run first, each class XCD-contiguous:
+// the launch puts the short tiles into the second class.
 // A problem split over K (ksplit > 1) runs its tiles once per K range kc,
 // the ranges outermost, so that concurrent tiles read the same K columns.
 __device__ __forceinline__ void decode_tile(const GemmBatch& args, int& pi, int& bt, int& tm, int& tn, int& kc,
@@ -173,25 +172,26 @@ __device__ __forceinline__ void decode_tile(const GemmBatch& args, int& pi, int&
   }
 }
 
-// Epilogues on the 128 x 128 accumulator tile.  The RoPE epilogue stages
-// the tile through LDS: rows 0..63 in tile_lo, rows 64..127 in tile_hi
-// (64 x 128 floats each).
-template <typename T>
-__device__ __forceinline__ void epilogue(const GemmProblem& P, int bt, int tm, int tn, f32x16_t (&acc)[2][2],
+// Epilogues on a tile of 64 IB x 64 JB, four waves (wm, wn) of 32 IB x 32 JB.
+// The RoPE epilogue (128 x 128 tiles only) stages the tile through LDS: rows
+// 0..63 in tile_lo, rows 64..127 in tile_hi (64 x 128 floats each).
+template <typename T, int IB, int JB>
+__device__ __forceinline__ void epilogue(const GemmProblem& P, int bt, int tm, int tn, f32x16_t (&acc)[IB][JB],
                                          float* tile_lo, float* tile_hi, int tid, int lane, int wm, int wn) {
   const int M = P.M, N = P.N;
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int m0 = tm * 64 * IB, n0 = tn * 64 * JB;
+  const int wr = m0 + wm * 32 * IB, wc = n0 + wn * 32 * JB;  // this wave's first row and column
   if (epi_direct(P.epi)) {
     const int e = P.epi;
     const T* __restrict__ bias = static_cast<const T*>(P.bias);
     const long long base = bt * P.strideC;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = n0 + wn * 64 + j * 32 + acc_col(lane);
+    for (int j = 0; j < JB; ++j) {
+      const int col = wc + j * 32 + acc_col(lane);
       if (col >= N) continue;
       const float bv = (e == EPI_GELU2 && bias) ? to_f32<T>(bias[col]) : 0.0f;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < IB; ++i) {
         // the factor or residual of all 16 entries first (clamped rows), so
         // that no load waits behind this lane's stores
         float f[16];
@@ -199,13 +199,13 @@ __device__ __forceinline__ void epilogue(const GemmProblem& P, int bt, int tm, i
           const T* __restrict__ aux = static_cast<const T*>(P.aux) + base;
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int row = min(m0 + wm * 64 + i * 32 + acc_row(r, lane), M - 1);
+            const int row = min(wr + i * 32 + acc_row(r, lane), M - 1);
             f[r] = to_f32<T>(aux[(long long)row * P.ldc + col]);
           }
         }
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = m0 + wm * 64 + i * 32 + acc_row(r, lane);
+          const int row = wr + i * 32 + acc_row(r, lane);
           if (row >= M) continue;
           const long long at = base + (long long)row * P.ldc + col;
           const float v = acc[i][j][r] + bv;
@@ -227,15 +227,15 @@ __device__ __forceinline__ void epilogue(const GemmProblem& P, int bt, int tm, i
     const T* __restrict__ bias = static_cast<const T*>(P.bias);
     const bool gelu = P.epi == EPI_BIAS_GELU;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = n0 + wn * 64 + j * 32 + acc_col(lane);
+    for (int j = 0; j < JB; ++j) {
+      const int col = wc + j * 32 + acc_col(lane);
       if (col >= N) continue;
       const float bv = bias ? to_f32<T>(bias[col]) : 0.0f;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < IB; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = m0 + wm * 64 + i * 32 + acc_row(r, lane);
+          const int row = wr + i * 32 + acc_row(r, lane);
           if (row >= M) continue;
           float v = acc[i][j][r] + bv;
           if (gelu) v = gelu_erf(v);
@@ -251,15 +251,15 @@ __device__ __forceinline__ void epilogue(const GemmProblem& P, int bt, int tm, i
     const bool diag = tm == tn;
     const bool vec4 = (P.ldc & 3) == 0;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = n0 + wn * 64 + j * 32 + acc_col(lane);
+    for (int j = 0; j < JB; ++j) {
+      const int col = wc + j * 32 + acc_col(lane);
       if (col >= N) continue;
       const float sc = rs[col];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < IB; ++i)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int row0 = m0 + wm * 64 + i * 32 + 8 * q + 4 * (lane >> 5);
+          const int row0 = wr + i * 32 + 8 * q + 4 * (lane >> 5);
           float v[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -277,7 +277,7 @@ __device__ __forceinline__ void epilogue(const GemmProblem& P, int bt, int tm, i
           }
         }
     }
-  } else {  // EPI_ROPE: stage the tile (plus the bias) in LDS so each thread sees both halves of a pair
+  } else if constexpr (IB == 2 && JB == 2) {  // EPI_ROPE: stage the tile (plus the bias) in LDS so each thread sees both halves of a pair
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int cl = wn * 64 + j * 32 + acc_col(lane);
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(NT) void gemm_kernel(const GemmBatch args) {
   }
 
   __syncthreads();  // the RoPE epilogue reuses the LDS tiles
-  epilogue<T>(P, bt, tm, tn, acc, reinterpret_cast<float*>(&smem[0][0][0]),
+  epilogue<T, 2, 2>(P, bt, tm, tn, acc, reinterpret_cast<float*>(&smem[0][0][0]),
               reinterpret_cast<float*>(&smem[2][0][0]), tid, lane, wm, wn);
 }
 
@@ -851,6 +851,98 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
     cosine_store<kDmaThreads>(P, bt, tm, tn, L, tid);
   else
     store_rows<BN, kDmaThreads>(P, bt, m0, n0, L, L, tid);
+}
+
+// ------------------------------------------------------------ float32 tiles
+// float32 products: 64 x 64 tiles, eight waves in two groups of four; in a
+// group each wave forms one 32 x 32 block (v_mfma_f32_32x32x2_f32), group g
+// over the K slices of 32 with kt % 2 = g, and the two sums are added in LDS
+// at the end.  The slices come by direct loads through a ring of four pairs
+// (32 KiB each).  The float32 matrix rate bounds it (a slice's products take
+// 1024 clocks on each SIMD, its operand reads 256 of LDS), so small tiles
+// cost nothing and fill the chip, and two waves per SIMD hide the reads and
+// the barriers of each other.
+// A 576 x 1024 x 4096 layer with its 576-token Gram matrix and the folds: 336
+// us on 128 x 128 tiles, 79 of them for 256 compute units, now about 75;
+// 4096 x 4096 x 4096 1.21 ms (113 TFLOP/s of about 150 that products on
+// registers alone reach).
+// Requirements (checked by the host): K % 32 == 0, lda and ldb multiples of
+// 4, A and B 16-byte aligned, no RoPE epilogue, K range or index map.
+constexpr int kF32 = 64;
+constexpr int kF32Pairs = 4;
+constexpr int kF32Threads = 512;
+
+__global__ __launch_bounds__(kF32Threads) void gemm_f32_kernel(const GemmBatch args) {
+  __shared__ uint4 st[kF32Pairs][2][2][kF32][8];  // per pair: slice of group 0, of group 1; each A rows, B rows
+  int pi, bt, tm, tn, kc, local;
+  decode_tile(args, pi, bt, tm, tn, kc, local);
+  const GemmProblem& P = args.p[pi];
+  if (P.run_if && P.run_if[bt] == 0) return;
+  const int M = P.M, N = P.N, m0 = tm * kF32, n0 = tn * kF32, nk = P.K / 32;
+  const float* __restrict__ A = static_cast<const float*>(P.A) + bt * P.strideA;
+  const float* __restrict__ B = static_cast<const float*>(P.B) + bt * P.strideB;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave >> 2, w4 = wave & 3, wm = w4 >> 1, wn = w4 & 1, lr = lane & 31, lh = lane >> 5;
+  const int np = (nk + 1) / 2, own = (nk - grp + 1) / 2;  // pairs; this group's slices
+  // wave w of a group moves rows 16 w .. 16 w + 15 of A and of B of its
+  // group's slices, one instruction per 8 rows (rows past the matrix read
+  // its last row; they are never stored)
+  const float* ga[2];
+  const float* gb[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int r = 16 * w4 + 8 * j + (lane >> 3), v = (lane & 7) ^ swz(r);
+    ga[j] = A + (long long)min(m0 + r, M - 1) * P.lda + 4 * v + 32 * grp;
+    gb[j] = B + (long long)min(n0 + r, N - 1) * P.ldb + 4 * v + 32 * grp;
+  }
+  const uint32_t wrow = lds_addr(&st[0][0][0][0][0]) + static_cast<uint32_t>(grp) * (2u * kF32 * 128u) +
+                        static_cast<uint32_t>(w4) * 16u * 128u;
+  auto issue = [&](int p) {
+    const uint32_t m = wrow + static_cast<uint32_t>(p % kF32Pairs) * (4u * kF32 * 128u);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      dma16(ga[j] + 64 * p, m + 1024u * j);
+      dma16(gb[j] + 64 * p, m + kF32 * 128u + 1024u * j);
+    }
+  };
+  f32x16_t acc[1][1];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.0f;
+  for (int p = 0; p < min(kF32Pairs - 1, own); ++p) issue(p);
+  for (int p = 0; p < np; ++p) {
+    // this wave's part of its group's slice p (past its last one: nothing is outstanding)
+    wait_vm_lgkm0(4 * max(0, min(kF32Pairs - 2, own - 1 - p)));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();  // every wave's part, and every wave is done with pair p - 1
+    asm volatile("" ::: "memory");
+    if (p + kF32Pairs - 1 < own) issue(p + kF32Pairs - 1);
+    if (p >= own) break;  // (the last pair of an odd count: group 1 has no slice)
+    const uint4 (*As)[8] = st[p % kF32Pairs][grp][0];
+    const uint4 (*Bs)[8] = st[p % kF32Pairs][grp][1];
+    float4 a[4], b[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {  // lane half lh covers k = 16 lh + 4 g + (0..3)
+      const int v = (4 * lh + g) ^ swz(lr);
+      a[g] = __builtin_bit_cast(float4, As[32 * wm + lr][v]);
+      b[g] = __builtin_bit_cast(float4, Bs[32 * wn + lr][v]);
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g][e], b[g][e], acc[0][0], 0, 0, 0);
+  }
+  __syncthreads();  // the ring is read out: group 1's sums pass through it
+  float* sums = reinterpret_cast<float*>(&st[0][0][0][0][0]) + w4 * 16 * 64 + lane;
+  if (grp) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sums[64 * r] = acc[0][0][r];
+  }
+  __syncthreads();
+  if (grp) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][0][r] += sums[64 * r];
+  epilogue<float, 1, 1>(P, bt, tm, tn, acc, nullptr, nullptr, tid, lane, wm, wn);
 }
 
 // ------------------------------------------------------------ 256 x 256 tiles
@@ -1420,21 +1512,30 @@ hipError_t launch_gram_reduce(const GemmProblem& partial, float* out, int ldc, c
                        s, partial, out, ldc, rs);
 }
 
-void gemm_finalize(GemmBatch& g) {
+static void finalize_tiles(GemmBatch& g, int tile) {
   int begin = 0;
   for (int i = 0; i < g.count; ++i) {
     GemmProblem& p = g.p[i];
-    p.tiles_m = (p.M + BM - 1) / BM;
-    p.tiles_n = (p.N + BN - 1) / BN;
+    p.tiles_m = (p.M + tile - 1) / tile;
+    p.tiles_n = (p.N + tile - 1) / tile;
     p.tiles_tri = p.triangular ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
     p.tiles_per_batch = p.tiles_tri * (p.ksplit > 1 ? p.ksplit : 1);
     p.tile_begin = begin;
     begin += p.tiles_per_batch * p.batch;
   }
   g.total_tiles = begin;
-  // a trailing cosine problem (the Gram matrix) runs after the others
-  g.first_tiles = g.count > 1 && g.p[g.count - 1].epi == EPI_COSINE ? g.p[g.count - 1].tile_begin : 0;
+  // Two classes of tiles, each spread evenly over the XCDs, the second
+  // dispatched after the first: trailing problems of at most half the first
+  // one's K (the weight folds) come last.  Dealt out with the long ones, 16
+  // short tiles on top of 248 long ones left seven XCDs 33 long tiles for
+  // their 32 compute units, a second wave of workgroups for one tile each
+  // (three 1225-token images: 69 us, now 52).
+  int q = g.count;
+  while (q > 1 && 2 * g.p[q - 1].K <= g.p[0].K) --q;
+  g.first_tiles = q < g.count ? g.p[q].tile_begin : 0;
 }
+
+void gemm_finalize(GemmBatch& g) { finalize_tiles(g, BM); }
 
 // K ranges of a split problem: equal ranges (K / ksplit) or kchunk-long ones
 // with a shorter last range, each a positive multiple of 256.
@@ -1502,19 +1603,16 @@ static bool big_tiles_pay(const GemmBatch& g) {
   return 23 * ((t256 + cus - 1) / cus) < 10 * ((t128 + cus - 1) / cus);
 }
 
-static void finalize_big(GemmBatch& g) {
-  int begin = 0;
+// Whether a float32 launch meets the float32 tiles' requirements.
+static bool f32_tiles_fit(const GemmBatch& g) {
   for (int i = 0; i < g.count; ++i) {
-    GemmProblem& p = g.p[i];
-    p.tiles_m = (p.M + kBig - 1) / kBig;
-    p.tiles_n = (p.N + kBig - 1) / kBig;
-    p.tiles_tri = p.triangular ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
-    p.tiles_per_batch = p.tiles_tri;
-    p.tile_begin = begin;
-    begin += p.tiles_per_batch * p.batch;
+    const GemmProblem& p = g.p[i];
+    if (p.epi == EPI_ROPE || p.epi == EPI_PARTIAL || p.ksplit > 1 || p.mapA || p.mapB || p.K % 32 != 0 ||
+        p.lda % 4 != 0 || p.ldb % 4 != 0 || p.strideA % 4 != 0 || p.strideB % 4 != 0 ||
+        (reinterpret_cast<uintptr_t>(p.A) & 15) != 0 || (reinterpret_cast<uintptr_t>(p.B) & 15) != 0)
+      return false;
   }
-  g.total_tiles = begin;
-  g.first_tiles = 0;
+  return true;
 }
 
 bool gemm_big_tiles(map_dtype dt, const GemmBatch& g) { return gemm_direct_loads(dt, g) && big_tiles_pay(g); }
@@ -1534,7 +1632,8 @@ hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipSt
     }
     if (dma && big_tiles_pay(g)) {
       GemmBatch q = g;
-      finalize_big(q);
+      finalize_tiles(q, kBig);
+      q.first_tiles = 0;
       return launch_kernel(name, g.norm_tiles ? gemm_big_kernel<true> : gemm_big_kernel<false>, dim3(q.total_tiles), dim3(kBigThreads), 0, s, q);
     }
     if (dma)
@@ -1543,6 +1642,11 @@ hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipSt
     for (int i = 0; i < g.count; ++i)  // index maps and K ranges exist in the direct-load kernel only
       if (g.p[i].epi == EPI_PARTIAL || g.p[i].mapA || g.p[i].mapB) return hipErrorInvalidValue;
     return launch_kernel(name, gemm_kernel<bf16_t>, dim3(g.total_tiles), dim3(NT), 0, s, g);
+  }
+  if (f32_tiles_fit(g)) {
+    GemmBatch q = g;
+    finalize_tiles(q, kF32);
+    return launch_kernel(name, gemm_f32_kernel, dim3(q.total_tiles), dim3(kF32Threads), 0, s, q);
   }
   return launch_kernel(name, gemm_kernel<float>, dim3(g.total_tiles), dim3(NT), 0, s, g);
 }

@@ -327,10 +327,10 @@ hipError_t enqueue_score(const map_weights& w, map_dtype dt, int B, int N, const
     g1.p[1].aux = gprime_t;
   }
   g1.count = 2;
+  if (extra_l1) g1.p[g1.count++] = *extra_l1;
+  // the folds last: their tiles are short where D_h is below D, and are then dispatched after the others
   g1.p[g1.count++] = linear(w.w_k, w.d_p, s.w2t_v, nullptr, s.wc_v, w.D_h, w.D_h, EPI_BIAS);  // W_K W2
   g1.p[g1.count++] = linear(w.w_q, w.d_p, s.w2t_t, nullptr, s.wc_t, w.D_h, w.D_h, EPI_BIAS);  // W_Q W2
-  // the Gram matrix last: its tiles are dispatched after every tile above
-  if (extra_l1) g1.p[g1.count++] = *extra_l1;
   gemm_finalize(g1);
   // The row norms: by prep, or (norms_in_layer1) inside the layer-1 launch:
   // with 256 x 256 tiles, by the first column of f_V's tiles from the

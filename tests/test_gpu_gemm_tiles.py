@@ -57,3 +57,21 @@ def test_big_tiles_row_norms(B, N, Dh):
         rep = oracle.replay_check(p[b], x["V_f32"][b], cfg.K, cfg.K0, cfg.tau, order[b], gain[b])
         assert rep.ok, f"image {b}: {rep.failure}"
         assert rep.max_gain_rel_err < 1e-5
+
+
+# float32 tiles (64 x 64, K in slices of 32 that two groups of waves take in
+# turn): one slice only, an odd count, more than the ring holds, one row past a
+# tile, and K that is no multiple of 32 (the register-staged kernel)
+@pytest.mark.parametrize("B,N,D", [(1, 65, 32), (2, 64, 96), (1, 129, 544), (3, 33, 4128), (1, 70, 40)])
+def test_f32_tiles_cosine(B, N, D):
+    from paper_2608_06411_amd import map_similarity
+    dev = device()
+    announce(f"float32 tiles, cosine B={B} N={N} D={D}")
+    g = torch.Generator(device=dev)
+    g.manual_seed(D)
+    V = torch.randn(B, N, D, generator=g, device=dev)
+    S, norms = map_similarity(V)
+    v = V.double() / V.double().norm(dim=2, keepdim=True)
+    for b in range(B):
+        assert float((S[b].double() - v[b] @ v[b].t()).abs().max()) < 1e-5
+        assert torch.equal(S[b], S[b].t())
