@@ -432,15 +432,16 @@ struct StagedTile {
 // 64 wn + 32 j), 256 threads; J = 1, eight waves (wm, wn) of 64 x 32 (rows
 // 64 wm + 32 i, columns 32 wn), 512 threads.  They go to LDS as they are;
 // the element-wise part runs on the way out, in one compact loop.
-template <int J>
+// IB = 1 (256 x 256 kernel only): the wave's first block alone, rows 32 wm.
+template <int J, int IB = 2>
 __device__ __forceinline__ void stage_acc(const f32x16_t (&acc)[2][J], const StagedTile& L, int lane, int wm, int wn) {
 #pragma unroll
   for (int j = 0; j < J; ++j)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < IB; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        L.row(wm * 64 + i * 32 + acc_row(r, lane))[wn * (32 * J) + j * 32 + acc_col(lane)] = acc[i][j][r];
+        L.row(wm * (32 * IB) + i * 32 + acc_row(r, lane))[wn * (32 * J) + j * 32 + acc_col(lane)] = acc[i][j][r];
 }
 
 __device__ __forceinline__ uint4 pack_bf16x8(const float (&f)[8]) {
@@ -475,11 +476,11 @@ __device__ __forceinline__ void store_bf16x8(bf16_t* dst, bool vec, int n, const
   }
 }
 
-// The row-wise epilogues over a staged tile of 128 rows by W = 128 or 256
+// The row-wise epilogues over a staged tile of ROWS rows by W = 128 or 256
 // columns (columns 0..127 in L0, 128.. in L1): bias (+ GELU), float32,
 // GELU and GELU' of acc + bias, acc times or plus the bf16 aux entry; every
 // global access moves 16 bytes along a row.
-template <int W, int NTH>
+template <int W, int NTH, int ROWS = BM>
 __device__ __forceinline__ void store_rows(const GemmProblem& P, int bt, int m0, int n0, const StagedTile& L0,
                                            const StagedTile& L1, int tid) {
   const int M = P.M, N = P.N, e = P.epi;
@@ -497,7 +498,7 @@ __device__ __forceinline__ void store_rows(const GemmProblem& P, int bt, int m0,
 #pragma unroll
   for (int k = 0; k < 8; ++k) bv[k] = biased && k < n ? bf16_to_f32(bias[col + k]) : 0.0f;
 #pragma unroll 2
-  for (int r = tid / (W / 8); r < BM; r += NTH / (W / 8)) {
+  for (int r = tid / (W / 8); r < ROWS; r += NTH / (W / 8)) {
     const int row = m0 + r;
     if (row >= M) break;
     const float* src = W > BN && c8 >= BN ? L1.row(r) + (c8 - BN) : L0.row(r) + c8;
@@ -531,6 +532,29 @@ __device__ __forceinline__ void store_rows(const GemmProblem& P, int bt, int m0,
       for (int k = 0; k < 8; ++k) f[k] = e == EPI_MUL ? f[k] * a8[k] : f[k] + a8[k];
     }
     store_bf16x8(static_cast<bf16_t*>(P.C) + at, vec, n, f);
+  }
+}
+
+// EPI_SILU: SiLU(gate) * up of a staged tile whose gate columns are in L0 and
+// whose up columns are in L1 (W = 128), or in L0's columns 0..63 and 64..127.
+template <int W, int NTH, int ROWS = BM>
+__device__ __forceinline__ void store_silu(const GemmProblem& P, int bt, int m0, int n0, const StagedTile& L0,
+                                           const StagedTile& L1, int tid) {
+  const long long base = bt * P.strideC;
+  const int c8 = (tid % (W / 8)) * 8, col = n0 + c8;
+  if (col >= P.N) return;
+  const int n = min(8, P.N - col);
+  const bool vec = n == 8 && (P.ldc & 7) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15) == 0 && (base & 7) == 0;
+#pragma unroll 2
+  for (int r = tid / (W / 8); r < ROWS; r += NTH / (W / 8)) {
+    const int row = m0 + r;
+    if (row >= P.M) break;
+    const float* g = L0.row(r) + c8;
+    const float* u = W == BN ? L1.row(r) + c8 : g + W;
+    float f[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) f[k] = g[k] / (1.0f + __expf(-g[k])) * u[k];
+    store_bf16x8(static_cast<bf16_t*>(P.C) + base + (long long)row * P.ldc + col, vec, n, f);
   }
 }
 
@@ -747,7 +771,8 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
   const int kl = P.ksplit > 1 ? (P.kchunk > 0 ? P.kchunk : P.K / P.ksplit) : P.K;
   const bf16_t* __restrict__ A = static_cast<const bf16_t*>(P.A) + bt * P.strideA + (long long)kc * kl;
   const bf16_t* __restrict__ B = static_cast<const bf16_t*>(P.B) + bt * P.strideB + (long long)kc * kl;
-  const int m0 = tm * BM, n0 = tn * BN;
+  const bool silu = P.epi == EPI_SILU;  // 64 gate columns, then the same columns of up (rows N.. of B)
+  const int m0 = tm * BM, n0 = tn * (silu ? BN / 2 : BN);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 2, wn = wave & 3;
   const int nk = min(kl, P.K - kc * kl) / 64;
@@ -769,7 +794,7 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
   for (int j = 0; j < 2; ++j) {
     const int r = 16 * wave + 8 * j + (lane >> 3);
     const int v = (lane & 7) ^ swz(r);  // the chunk the swizzle puts at position lane & 7 of row r
-    const int ra = min(m0 + r, M - 1), rb = min(n0 + r, N - 1);
+    const int ra = min(m0 + r, M - 1), rb = silu ? (r < 64 ? min(n0 + r, N - 1) : N + min(n0 + r - 64, N - 1)) : min(n0 + r, N - 1);
     ga[j] = A + (long long)(mapA ? mapA[ra] : ra) * P.lda + 8 * v;
     gb[j] = B + (long long)(mapB ? mapB[rb] : rb) * P.ldb + 8 * v;
   }
@@ -849,6 +874,8 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
   __syncthreads();
   if (P.epi == EPI_COSINE)
     cosine_store<kDmaThreads>(P, bt, tm, tn, L, tid);
+  else if (silu)
+    store_silu<BN / 2, kDmaThreads>(P, bt, m0, n0, L, L, tid);
   else
     store_rows<BN, kDmaThreads>(P, bt, m0, n0, L, L, tid);
 }
@@ -996,13 +1023,25 @@ __device__ __forceinline__ void phase_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// NORMS: the launch has row norms to form (args.norm_tiles).
-template <bool NORMS>
+// Tile heights.  A launch whose tiles do not fill whole rounds of workgroups
+// would leave compute units idle in its last one, so a problem's rows may also
+// be cut into tiles of 192 or 128 rows (GemmProblem::th):
+//   TM = 192: the lower half-tile of A is 64 rows (wave (wm, wn): rows 128 +
+//       32 wm + (0..31)), the last two phases have half the products;
+//   128 rows or fewer in a tile: two phases a slice (no lower half), the
+//       slices in a ring of three.
+// @@COST@@
+//
+// NORMS: the launch has row norms to form (GemmProblem::norm_at).
+template <bool NORMS, int TM>
 __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch args) {
-  // [buffer][half-tile: A rows 0..127, A rows 128.., B rows 0..127, B rows 128..]
-  __shared__ uint4 half[2][4][BM][8];
+  // Half-tile arrays.  More than 128 rows: 4 buffer + (A rows 0..127, A rows
+  // 128.., B rows 0..127, B rows 128..), buffer = 0, 1; else 3 slot + (A, B
+  // rows 0..127, B rows 128..), slot = 0, 1, 2.
+  __shared__ uint4 half[9][BM][8];
   __shared__ float rs_big[2 * kBig];  // cosine: 1/norm of the tile's rows, then columns
-  const int tile = xcd_remap(blockIdx.x, args.total_tiles);
+  const int f = args.first_tiles, blk = blockIdx.x;
+  const int tile = blk < f ? xcd_remap(blk, f) : f + xcd_remap(blk - f, args.total_tiles - f);
   int pi = 0;
 #pragma unroll
   for (int q = 1; q < kMaxGemmProblems; ++q)
@@ -1022,7 +1061,9 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
     tn = in / rows;
   }
   if (P.run_if && P.run_if[bt] == 0) return;
-  const int M = P.M, N = P.N, m0 = tm * kBig, n0 = tn * kBig;
+  const int M = P.M, N = P.N, m0 = tm * P.th;
+  const bool silu = P.epi == EPI_SILU;  // 128 gate columns, then the same columns of up (rows N.. of B)
+  const int n0 = tn * (silu ? kBig / 2 : kBig);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
   const int nk = P.K / 64;  // a multiple of 4 (checked by the host)
@@ -1047,16 +1088,25 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
     for (int j = 0; j < 2; ++j) {
       const int r = 16 * wave + 8 * j + (lane >> 3);
       const int v = (lane & 7) ^ swz(r);  // the chunk the swizzle puts at position lane & 7 of row r
-      const int ra = min(128 * x + r, M - 1 - m0), rb = min(128 * x + r, N - 1 - n0);
-      off[x][j] = static_cast<uint32_t>(mapA ? mapA[m0 + ra] : ra) * static_cast<uint32_t>(2 * P.lda) + 16u * v;
+      // (TM = 192: the lower half-tile has 8 rows per wave, one instruction)
+      const int r1 = TM == 192 && x == 1 ? 8 * wave + (lane >> 3) : r, va = (lane & 7) ^ swz(r1);
+      const int ra = min(128 * x + r1, M - 1 - m0), rb = silu ? min(r, N - 1 - n0) + x * N : min(128 * x + r, N - 1 - n0);
+      off[x][j] = static_cast<uint32_t>(mapA ? mapA[m0 + ra] : ra) * static_cast<uint32_t>(2 * P.lda) + 16u * va;
       off[2 + x][j] = static_cast<uint32_t>(mapB ? mapB[n0 + rb] : rb) * static_cast<uint32_t>(2 * P.ldb) + 16u * v;
     }
-  const uint32_t wrow = lds_addr(&half[0][0][0][0]) + static_cast<uint32_t>(wave) * 16u * 128u;
-  auto issue = [&](int kt, int buf, int x) {  // half-tile x of slice kt into buffer buf
+  const uint32_t wrow = lds_addr(&half[0][0][0]) + static_cast<uint32_t>(wave) * 16u * 128u;
+  auto issue_at = [&](int kt, int x, int at) {  // half-tile x of slice kt into array `at`
     const char* src = (x < 2 ? baseA : baseB) + 128LL * kt;
-    const uint32_t m = wrow + static_cast<uint32_t>(4 * buf + x) * (BM * 128u);
+    const uint32_t m = wrow + static_cast<uint32_t>(at) * (BM * 128u);
     dma16_off(src, off[x][0], m);
     dma16_off(src, off[x][1], m + 1024u);
+  };
+  auto issue = [&](int kt, int buf, int x) {  // half-tile x of slice kt into buffer buf
+    if (TM == 192 && x == 1)
+      dma16_off(baseA + 128LL * kt, off[1][0],
+                wrow + static_cast<uint32_t>(4 * buf + 1) * (BM * 128u) - static_cast<uint32_t>(wave) * 8u * 128u);
+    else
+      issue_at(kt, x, 4 * buf + x);
   };
 
   f32x16_t acc[2][2][2][1];  // [i][j][block]: rows 128 i + 64 wm + 32 block, columns 128 j + 32 wn
@@ -1070,23 +1120,25 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
         for (int r = 0; r < 16; ++r) acc[i][j][b][0][r] = 0.0f;
   const int lr = lane & 31, lh = lane >> 5;
   bf16x8_t a[2][4], b0[4], b1[4];  // [block][step of 16]
-  auto read_a = [&](int buf, int i) {
+  constexpr int kLow = TM == 192 ? 1 : 2;  // blocks of a wave in the lower half-tile
+  auto read_a = [&](int at, int i) {       // from array `at`: rows of the upper (i = 0) or lower half
+    const int nb = i ? kLow : 2;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < nb; ++b)
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const int r = 64 * wm + 32 * b + lr;
-        a[b][s] = __builtin_bit_cast(bf16x8_t, half[buf][i][r][(2 * s + lh) ^ swz(lr)]);
+        const int r = 32 * nb * wm + 32 * b + lr;
+        a[b][s] = __builtin_bit_cast(bf16x8_t, half[at][r][(2 * s + lh) ^ swz(lr)]);
       }
   };
-  auto read_b = [&](int buf, int j, bf16x8_t (&b)[4]) {
+  auto read_b = [&](int at, bf16x8_t (&b)[4]) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int r = 32 * wn + lr;
-      b[s] = __builtin_bit_cast(bf16x8_t, half[buf][2 + j][r][(2 * s + lh) ^ swz(lr)]);
+      b[s] = __builtin_bit_cast(bf16x8_t, half[at][r][(2 * s + lh) ^ swz(lr)]);
     }
   };
-  // Row norms (args.norm_tiles).  Row block (i, b) = rows 128 i + 64 wm +
+  // Row norms (GemmProblem::norm_at).  Row block (i, b) = rows 128 i + 64 wm +
   // 32 b + (0..31) of both wm is summed by the tiles of column (2 i + b) mod
   // min(tiles_n, 4), wave wn taking step wn of 16 of every slice (lane l: row
   // l & 31, eight of the step's values), in float32, slice after slice; the
@@ -1094,19 +1146,19 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
   // instructions per slice, which fit beside the other group's products.
   // (With all of it on the first tile column, 64 instructions in half of its
   // waves, each of its slices took 9 % longer, and with it every round.)
-  const int ncol = NORMS && args.norm_tiles == pi + 1 ? min(P.tiles_n, 4) : 0;
+  const int ncol = NORMS && P.norm_at ? min(P.tiles_n, 4) : 0;
   bool sq[2][2];
   float nacc[2][2] = {{0.0f, 0.0f}, {0.0f, 0.0f}};
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) sq[i][b] = tn < ncol && (2 * i + b) % ncol == tn;
-  auto squares = [&](int buf, int i) {
+    for (int b = 0; b < 2; ++b) sq[i][b] = tn < ncol && (2 * i + b) % max(ncol, 1) == tn;
+  auto squares = [&](int at, int i) {
     if constexpr (!NORMS) return;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       if (!sq[i][b]) continue;
-      const uint4 u = half[buf][i][64 * wm + 32 * b + lr][(2 * wn + lh) ^ swz(lr)];
+      const uint4 u = half[at][64 * wm + 32 * b + lr][(2 * wn + lh) ^ swz(lr)];
       const uint32_t wv[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -1120,7 +1172,7 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
+      for (int c = 0; c < (i ? kLow : 2); ++c)
         acc[i][j][c][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c][s], b[s], acc[i][j][c][0], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
   };
@@ -1132,9 +1184,9 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
   // phase, before the barrier that lets either group read it.
   auto slice = [&](int kt, int buf) {
     const bool more1 = kt + 1 < nk, more2 = kt + 2 < nk;
-    read_b(buf, 0, b0);
+    read_b(4 * buf + 2, b0);
     __builtin_amdgcn_sched_barrier(0);
-    read_a(buf, 0);
+    read_a(4 * buf, 0);
     if (more1) issue(kt + 1, buf ^ 1, 1);
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt lgkmcnt(8)" ::: "memory");
@@ -1144,16 +1196,16 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
     products(0, 0, b0);
     phase_barrier();
 
-    read_b(buf, 1, b1);
+    read_b(4 * buf + 3, b1);
     if (more2) issue(kt + 2, buf, 2);
-    squares(buf, 0);
+    squares(4 * buf, 0);
     phase_barrier();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     products(0, 1, b1);
     phase_barrier();
 
-    read_a(buf, 1);
+    read_a(4 * buf + 1, 1);
     if (more2) issue(kt + 2, buf, 0);
     phase_barrier();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1163,60 +1215,108 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
 
     if (more2) {
       issue(kt + 2, buf, 3);
-      squares(buf, 1);
+      squares(4 * buf + 1, 1);
       asm volatile("s_waitcnt vmcnt(6)" ::: "memory");  // all but the three half-tiles of slice kt + 2
     } else {
-      squares(buf, 1);
+      squares(4 * buf + 1, 1);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     phase_barrier();
     products(1, 1, b1);
     phase_barrier();
   };
-  issue(0, 0, 2);
-  issue(0, 0, 0);
-  issue(0, 0, 3);
-  issue(0, 0, 1);
-  issue(1, 1, 2);
-  issue(1, 1, 0);
-  issue(1, 1, 3);
-  asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-  phase_barrier();
-  if (wm) phase_barrier();  // group 1 runs one barrier behind group 0
-  for (int kt = 0; kt < nk; kt += 2) {
-    slice(kt, 0);
-    slice(kt + 1, 1);
+  // One slice of a tile of at most 128 rows, in ring slot kt % 3.  The slot
+  // that slice kt + 2 goes to held slice kt - 1, whose last reads each group
+  // waited for before a barrier that both have passed; slice kt + 1 has
+  // landed before the barrier that lets either group read it.
+  auto slice_low = [&](int kt, int slot, int refill) {
+    const bool more = kt + 2 < nk;
+    read_b(3 * slot + 1, b0);
+    read_a(3 * slot, 0);
+    if (more) {
+      issue_at(kt + 2, 0, 3 * refill);
+      issue_at(kt + 2, 2, 3 * refill + 1);
+      issue_at(kt + 2, 3, 3 * refill + 2);
+    }
+    squares(3 * slot, 0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    phase_barrier();
+    products(0, 0, b0);
+    phase_barrier();
+
+    read_b(3 * slot + 2, b1);
+    if (more)
+      asm volatile("s_waitcnt vmcnt(6)" ::: "memory");  // all but slice kt + 2
+    else
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    phase_barrier();
+    products(0, 1, b1);
+    phase_barrier();
+  };
+  const bool low = min(P.th, M - m0) <= 128;  // (uniform over the workgroup)
+  if (low) {
+    issue_at(0, 0, 0);
+    issue_at(0, 2, 1);
+    issue_at(0, 3, 2);
+    issue_at(1, 0, 3);
+    issue_at(1, 2, 4);
+    issue_at(1, 3, 5);
+    asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+    phase_barrier();
+    if (wm) phase_barrier();  // group 1 runs one barrier behind group 0
+    int slot = 0;
+#pragma unroll 1
+    for (int kt = 0; kt < nk; ++kt) {
+      slice_low(kt, slot, slot == 0 ? 2 : slot - 1);
+      slot = slot == 2 ? 0 : slot + 1;
+    }
+  } else {
+    issue(0, 0, 2);
+    issue(0, 0, 0);
+    issue(0, 0, 3);
+    issue(0, 0, 1);
+    issue(1, 1, 2);
+    issue(1, 1, 0);
+    issue(1, 1, 3);
+    asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+    phase_barrier();
+    if (wm) phase_barrier();  // group 1 runs one barrier behind group 0
+    for (int kt = 0; kt < nk; kt += 2) {
+      slice(kt, 0);
+      slice(kt + 1, 1);
+    }
   }
   if (!wm) phase_barrier();
   __syncthreads();  // the buffers are free
   if (NORMS && tn < ncol) {
-    float* sums = reinterpret_cast<float*>(&half[0][0][0][0]);  // [2 i + b][wm][wn][lh][32]
+    float* sums = reinterpret_cast<float*>(&half[0][0][0]);  // [2 i + b][wm][wn][lh][32]
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       if (sq[q >> 1][q & 1]) sums[(8 * q + wave) * 64 + lane] = nacc[q >> 1][q & 1];
     __syncthreads();
     const int q = tid >> 6, row = 128 * (q >> 1) + 32 * (q & 1) + 64 * (lane >> 5) + lr;  // threads 0..255
-    if (q < 4 && q % ncol == tn && m0 + row < M) {
+    if (q < 4 && q % max(ncol, 1) == tn && row < P.th && m0 + row < M) {
       float t = 0.0f;
 #pragma unroll
       for (int k = 0; k < 8; ++k) t += sums[(8 * q + 4 * (lane >> 5)) * 64 + 32 * k + lr];
       const float n = sqrtf(t);
-      args.norms[m0 + row] = n;
-      args.ninv[m0 + row] = n > 0.0f ? 1.0f / n : 0.0f;
+      args.norms[P.norm_at - 1 + m0 + row] = n;
+      args.ninv[P.norm_at - 1 + m0 + row] = n > 0.0f ? 1.0f / n : 0.0f;
     }
     __syncthreads();
   }
-  float* stage0 = reinterpret_cast<float*>(&half[0][0][0][0]);
-  float* stage1 = reinterpret_cast<float*>(&half[1][0][0][0]);
+  float* stage0 = reinterpret_cast<float*>(&half[0][0][0]);
+  float* stage1 = reinterpret_cast<float*>(&half[4][0][0]);
   if (P.epi == EPI_COSINE) {
     rs_big[tid] = rs_mine;
     const StagedTile LC{stage0, stage0 + 64 * BN, stage1, stage1 + 64 * BM};
 #pragma unroll 1
     for (int q = 0; q < 4; ++q) {
-      const int i = q >> 1, j = q & 1, TM = 2 * tm + i, TN = 2 * tn + j;  // the sub-tile in 128 x 128 tiles
+      const int i = q >> 1, j = q & 1, tm1 = 2 * tm + i, tn1 = 2 * tn + j;  // the sub-tile in 128 x 128 tiles
       // (uniform over the workgroup; a diagonal tile's sub-tile below the
       // diagonal is the mirror of the one above it)
-      if (TM > TN || TM * BM >= M || TN * BN >= N) continue;
+      if (tm1 > tn1 || tm1 * BM >= M || tn1 * BN >= N) continue;
       __syncthreads();  // the staging is free (and rs_big written)
       const float *rr = rs_big + 128 * i, *rc = rs_big + kBig + 128 * j;
       if (q == 0)
@@ -1228,26 +1328,28 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
       else
         cosine_stage<1>(acc[1][1], LC, rr, rc, lane, wm, wn);
       __syncthreads();
-      cosine_store<kBigThreads>(P, bt, TM, TN, LC, tid);
+      cosine_store<kBigThreads>(P, bt, tm1, tn1, LC, tid);
     }
     return;
   }
-  // 128 rows by 256 columns at a time
+  // 128 rows by 256 columns at a time (the lower half of TM = 192: 64)
   const StagedTile L0{stage0, stage0 + 64 * BN, nullptr, nullptr}, L1{stage1, stage1 + 64 * BN, nullptr, nullptr};
-#pragma unroll 1
-  for (int i = 0; i < 2; ++i) {
-    if (m0 + 128 * i >= M) break;
-    if (i == 0) {
-      stage_acc<1>(acc[0][0], L0, lane, wm, wn);
-      stage_acc<1>(acc[0][1], L1, lane, wm, wn);
-    } else {
-      __syncthreads();  // the staging is read out
-      stage_acc<1>(acc[1][0], L0, lane, wm, wn);
-      stage_acc<1>(acc[1][1], L1, lane, wm, wn);
-    }
-    __syncthreads();
-    store_rows<kBig, kBigThreads>(P, bt, m0 + 128 * i, n0, L0, L1, tid);
-  }
+  stage_acc<1>(acc[0][0], L0, lane, wm, wn);
+  stage_acc<1>(acc[0][1], L1, lane, wm, wn);
+  __syncthreads();
+  if (silu)
+    store_silu<kBig / 2, kBigThreads>(P, bt, m0, n0, L0, L1, tid);
+  else
+    store_rows<kBig, kBigThreads>(P, bt, m0, n0, L0, L1, tid);
+  if (low) return;
+  __syncthreads();  // the staging is read out
+  stage_acc<1, kLow>(acc[1][0], L0, lane, wm, wn);
+  stage_acc<1, kLow>(acc[1][1], L1, lane, wm, wn);
+  __syncthreads();
+  if (silu)
+    store_silu<kBig / 2, kBigThreads, 64 * kLow>(P, bt, m0 + 128, n0, L0, L1, tid);
+  else
+    store_rows<kBig, kBigThreads, 64 * kLow>(P, bt, m0 + 128, n0, L0, L1, tid);
 }
 
 // Projection to d_p <= 128 columns with the RoPE epilogue (the keys and
@@ -1512,18 +1614,31 @@ hipError_t launch_gram_reduce(const GemmProblem& partial, float* out, int ldc, c
                        s, partial, out, ldc, rs);
 }
 
-static void finalize_tiles(GemmBatch& g, int tile) {
+// Tiles of `wide` columns over a problem's columns (EPI_SILU: half of a
+// tile's columns are gate columns, the other half their up columns).
+static int col_tiles(const GemmProblem& p, int wide) {
+  if (p.epi == EPI_SILU) wide /= 2;
+  return (p.N + wide - 1) / wide;
+}
+
+// Tile counts and order of a problem list with tiles of p.th rows by `wide` columns.
+static void count_tiles(GemmBatch& g, int wide) {
   int begin = 0;
   for (int i = 0; i < g.count; ++i) {
     GemmProblem& p = g.p[i];
-    p.tiles_m = (p.M + tile - 1) / tile;
-    p.tiles_n = (p.N + tile - 1) / tile;
+    p.tiles_m = (p.M + p.th - 1) / p.th;
+    p.tiles_n = col_tiles(p, wide);
     p.tiles_tri = p.triangular ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
     p.tiles_per_batch = p.tiles_tri * (p.ksplit > 1 ? p.ksplit : 1);
     p.tile_begin = begin;
     begin += p.tiles_per_batch * p.batch;
   }
   g.total_tiles = begin;
+}
+
+static void finalize_tiles(GemmBatch& g, int tile) {
+  for (int i = 0; i < g.count; ++i) g.p[i].th = tile;
+  count_tiles(g, tile);
   // Two classes of tiles, each spread evenly over the XCDs, the second
   // dispatched after the first: trailing problems of at most half the first
   // one's K (the weight folds) come last.  Dealt out with the long ones, 16
@@ -1548,7 +1663,7 @@ static bool k_ranges_ok(const GemmProblem& p) {
 // The epilogues of the direct-load kernel (the RoPE epilogue runs in the
 // register-staged kernel or the projection kernel).
 static bool dma_epilogue(int e) {
-  return e == EPI_BIAS_GELU || e == EPI_BIAS || e == EPI_COSINE || e == EPI_PARTIAL || epi_direct(e);
+  return e == EPI_BIAS_GELU || e == EPI_BIAS || e == EPI_COSINE || e == EPI_PARTIAL || e == EPI_SILU || epi_direct(e);
 }
 
 bool gemm_direct_loads(map_dtype dt, const GemmBatch& g) {
@@ -1576,31 +1691,133 @@ static int gemm_cus() {
   return cached[dev];
 }
 
-// 256 x 256 tiles for a direct-load launch whose problems all have a
-// row-wise epilogue (bias, GELU, float32, GELU', product, residual) or are a
-// Gram matrix's upper triangle (cosine), and no K split, when they take
-// fewer waves of workgroups: a wave of 256 x 256
-// tiles costs about 2.3 waves of 128 x 128 tiles (measured on the first
-// layer's and the decoder layer's shapes).
-static bool big_tiles_pay(const GemmBatch& g) {
-  if (g.norm_blocks) return false;
+// Costs of a tile, in hundredths of a 256 x 256 tile over the same K.
+constexpr int kCost256 = 100, kCost192 = 79, kCost128 = 56;
+constexpr int kCostSmall = 43;  // a 128 x 128 tile of the other kernel
+
+// Time of `full` tiles of cost c, dispatched first, and `low` tiles of 128
+// rows after them, one tile at a time on each of `cus` units.
+static long long makespan(long long full, long long c, long long low, long long cus) {
+  const long long rounds = full / cus, rem = full % cus;
+  long long t = rounds * c;
+  if (rem) {  // the units free in the last round of full tiles take low ones meanwhile
+    t += c;
+    low -= (cus - rem) * std::max(1LL, (c + c / 8) / kCost128);
+  }
+  return t + (low > 0 ? (low + cus - 1) / cus * kCost128 : 0);
+}
+
+// The tiles of 256 columns for a launch: whether they apply (row-wise
+// epilogues and upper triangles with the cosine epilogue, no K split), their
+// cost, and the launch's problem list q with tile heights `tm` or, dispatched
+// after those, 128 rows.  The largest problem without an upper triangle is
+// cut at the multiple of tm that lets the last round of workgroups end
+// earliest; the others' tiles count as they are.
+static long long plan_big(const GemmBatch& g, GemmBatch& q, int& tm) {
+  if (g.norm_blocks) return -1;
   for (int i = 0; i < g.count; ++i)  // its loads' 32-bit byte offsets (an index map reaches kSubsetMaxN rows)
-    if (g.p[i].lda > (1 << 17) || g.p[i].ldb > (1 << 17)) return false;
-  if (g.norm_tiles > 0 && (g.norm_tiles > g.count || g.p[g.norm_tiles - 1].batch != 1)) return false;
-  long long t128 = 0, t256 = 0;
+    if (g.p[i].lda > (1 << 17) || g.p[i].ldb > (1 << 17) ||
+        (g.p[i].epi == EPI_SILU && 2LL * g.p[i].ldb * (g.p[i].N + kBig) > INT32_MAX))
+      return -1;
+  if (g.norm_tiles > 0 && (g.norm_tiles > g.count || g.p[g.norm_tiles - 1].batch != 1)) return -1;
+  int cut = -1, same = 0;  // the problem to cut; whether every problem has row-wise tiles
+  long long most = 0;
   for (int i = 0; i < g.count; ++i) {
     const GemmProblem& p = g.p[i];
     const bool gram = p.epi == EPI_COSINE && p.triangular && p.M == p.N;
-    if (!(p.epi == EPI_BIAS || p.epi == EPI_BIAS_GELU || epi_direct(p.epi) || gram) || p.ksplit > 1 ||
+    if (!(p.epi == EPI_BIAS || p.epi == EPI_BIAS_GELU || p.epi == EPI_SILU || epi_direct(p.epi) || gram) || p.ksplit > 1 ||
         (p.triangular && !gram))
-      return false;
-    const long long a = (p.M + 127) / 128, b = (p.N + 127) / 128;
-    const long long c = (p.M + kBig - 1) / kBig, d = (p.N + kBig - 1) / kBig;
-    t128 += (gram ? a * (a + 1) / 2 : a * b) * p.batch;
-    t256 += (gram ? c * (c + 1) / 2 : c * d) * p.batch;
+      return -1;
+    same += !gram;
+    const long long work = (long long)p.M * p.N * p.K;
+    if (!gram && !p.mapA && p.batch == 1 && work > most) {
+      most = work;
+      cut = i;
+    }
   }
   const long long cus = gemm_cus();
-  return 23 * ((t256 + cus - 1) / cus) < 10 * ((t128 + cus - 1) / cus);
+  long long best = -1;
+  int best_tm = kBig, best_rows = 0;
+  for (const int t : {256, 192}) {
+    if (t == 192 && (same < g.count || g.norm_tiles)) continue;
+    const long long c = t == 256 ? kCost256 : kCost192;
+    long long full = 0, low = 0;  // of the problems that stay whole
+    for (int i = 0; i < g.count; ++i) {
+      const GemmProblem& p = g.p[i];
+      const long long a = (p.M + t - 1) / t, b = col_tiles(p, kBig);
+      if (i == cut) continue;
+      if (p.triangular) full += a * (a + 1) / 2 * p.batch;
+      else if (p.M <= 128 || 2 * p.K <= g.p[0].K) low += a * b * p.batch;
+      else full += a * b * p.batch;
+    }
+    const int M = cut >= 0 ? g.p[cut].M : 0;
+    const long long b = cut >= 0 ? col_tiles(g.p[cut], kBig) : 0;
+    for (int f = M / t + (M % t > 128); f >= 0; --f) {  // f tile rows of t, the rest of 128
+      const int rest = std::max(0, M - f * t);
+      const long long cost = makespan(full + f * b, c, low + (rest + 127) / 128 * b, cus);
+      if (best < 0 || cost < best) {
+        best = cost;
+        best_tm = t;
+        best_rows = std::min(M, f * t);
+      }
+      if (cut < 0) break;
+    }
+  }
+  tm = best_tm;
+  // the problem list: full tiles, then tiles of 128 rows and short sums
+  q = g;
+  q.count = 0;
+  q.norm_tiles = g.norm_tiles;
+  for (int late = 0; late < 2; ++late) {
+    if (late) q.first_tiles = q.count;  // (a problem index until the tiles are counted)
+    for (int i = 0; i < g.count; ++i) {
+      GemmProblem p = g.p[i];
+      p.norm_at = g.norm_tiles == i + 1 ? 1 : 0;
+      p.th = best_tm;
+      if (i == cut) {
+        if (late ? best_rows == p.M : best_rows == 0) continue;
+        if (late) {
+          p.th = 128;
+          p.A = static_cast<const bf16_t*>(p.A) + (long long)best_rows * p.lda;
+          const long long at = (long long)best_rows * p.ldc;
+          p.C = static_cast<char*>(p.C) + at * (p.epi == EPI_F32 ? 4 : 2);
+          if (p.aux) p.aux = static_cast<char*>(p.aux) + at * 2;
+          if (p.norm_at) p.norm_at += best_rows;
+          p.M -= best_rows;
+        } else {
+          p.M = best_rows;
+        }
+      } else if (late != (!p.triangular && (p.M <= 128 || 2 * p.K <= g.p[0].K) ? 1 : 0)) {
+        continue;
+      }
+      q.p[q.count++] = p;
+    }
+  }
+  const int first = q.first_tiles;
+  count_tiles(q, kBig);
+  q.first_tiles = first > 0 && first < q.count ? q.p[first].tile_begin : 0;
+  return best;
+}
+
+// 128 x 128 tiles' time in the same units: rounds of the long tiles, then
+// what the units free in the last one have not taken of the short sums.
+static long long small_tiles_cost(const GemmBatch& g) {
+  long long full = 0, brief = 0, kb = 1;
+  for (int i = 0; i < g.count; ++i) {
+    const GemmProblem& p = g.p[i];
+    const long long a = (p.M + 127) / 128, b = col_tiles(p, BN), n = (p.triangular ? a * (a + 1) / 2 : a * b) * p.batch;
+    const bool late = i > 0 && 2 * p.K <= g.p[0].K;
+    (late ? brief : full) += n;
+    if (late) kb = std::max<long long>(kb, p.K);
+  }
+  const long long cus = gemm_cus(), rounds = (full + cus - 1) / cus, k0 = std::max(1, g.p[0].K);
+  const long long left = std::max(0LL, brief - (rounds * cus - full) * (k0 / kb));
+  return rounds * kCostSmall + (left + cus - 1) / cus * (kCostSmall * kb / k0);
+}
+
+static bool big_tiles_pay(const GemmBatch& g, GemmBatch& q, int& tm) {
+  const long long big = plan_big(g, q, tm);
+  return big >= 0 && big < small_tiles_cost(g);
 }
 
 // Whether a float32 launch meets the float32 tiles' requirements.
@@ -1615,32 +1832,28 @@ static bool f32_tiles_fit(const GemmBatch& g) {
   return true;
 }
 
-bool gemm_big_tiles(map_dtype dt, const GemmBatch& g) { return gemm_direct_loads(dt, g) && big_tiles_pay(g); }
+bool gemm_big_tiles(map_dtype dt, const GemmBatch& g) {
+  GemmBatch q;
+  int tm;
+  return gemm_direct_loads(dt, g) && big_tiles_pay(g, q, tm);
+}
 
 hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipStream_t s) {
   if (g.total_tiles == 0) return hipSuccess;
   // the in-tile row norms exist in the 256 x 256 kernel only
   if (g.norm_tiles > 0 && !gemm_big_tiles(dt, g)) return hipErrorInvalidValue;
   if (dt == MAP_BF16) {
-    bool dma = true;  // every problem meets the direct-load requirements
-    for (int i = 0; i < g.count; ++i) {
-      const GemmProblem& p = g.p[i];
-      dma = dma && dma_epilogue(p.epi) && p.K % 256 == 0 && p.lda % 8 == 0 && p.ldb % 8 == 0 &&
-            (reinterpret_cast<uintptr_t>(p.A) & 15) == 0 && (reinterpret_cast<uintptr_t>(p.B) & 15) == 0 &&
-            p.strideA % 8 == 0 && p.strideB % 8 == 0 &&
-            k_ranges_ok(p);
-    }
-    if (dma && big_tiles_pay(g)) {
-      GemmBatch q = g;
-      finalize_tiles(q, kBig);
-      q.first_tiles = 0;
-      return launch_kernel(name, g.norm_tiles ? gemm_big_kernel<true> : gemm_big_kernel<false>, dim3(q.total_tiles), dim3(kBigThreads), 0, s, q);
-    }
+    const bool dma = gemm_direct_loads(dt, g);
+    GemmBatch q;
+    int tm;
+    if (dma && big_tiles_pay(g, q, tm))
+      return launch_kernel(name, g.norm_tiles ? gemm_big_kernel<true, 256> : tm == 192 ? gemm_big_kernel<false, 192> : gemm_big_kernel<false, 256>,
+                           dim3(q.total_tiles), dim3(kBigThreads), 0, s, q);
     if (dma)
       return launch_kernel(name, gemm_dma_kernel, dim3(g.total_tiles + g.norm_blocks), dim3(kDmaThreads), 0, s, g);
     if (g.norm_blocks) return hipErrorInvalidValue;
     for (int i = 0; i < g.count; ++i)  // index maps and K ranges exist in the direct-load kernel only
-      if (g.p[i].epi == EPI_PARTIAL || g.p[i].mapA || g.p[i].mapB) return hipErrorInvalidValue;
+      if (g.p[i].epi == EPI_PARTIAL || g.p[i].epi == EPI_SILU || g.p[i].mapA || g.p[i].mapB) return hipErrorInvalidValue;
     return launch_kernel(name, gemm_kernel<bf16_t>, dim3(g.total_tiles), dim3(NT), 0, s, g);
   }
   if (f32_tiles_fit(g)) {

@@ -80,6 +80,8 @@ enum EpiMode : int {
   EPI_GELU2 = 6,      // v = acc + bias[n]: C[m][n] = GELU(v) and aux[m][n] = GELU'(v), both stored as T
   EPI_MUL = 7,        // C[m][n] = acc * aux[m][n] (aux of type T, leading dimension ldc), stored as T
   EPI_RESID = 8,      // C[m][n] = acc + aux[m][n] (a residual connection), stored as T
+  EPI_SILU = 9,       // C[m][n] = SiLU(A B[n]) * (A B[N + n]): B has 2 N rows, gate then up (bf16
+                      // direct-load kernels)
 };
 // Epilogues written lane by lane in registers (no staging): every kernel runs them.
 __host__ __device__ inline bool epi_direct(int e) { return e >= EPI_F32 && e <= EPI_RESID; }
@@ -108,9 +110,11 @@ struct GemmProblem {
                            // (each [M][ldc] of type T)
   // filled by the host helper
   int tiles_m, tiles_n, tiles_tri, tiles_per_batch, tile_begin;
+  int th;       // rows of a tile
+  int norm_at;  // 256-column tiles: 1 + the row of norms that row 0 of A has (0: no norms)
 };
 
-constexpr int kMaxGemmProblems = 6;
+constexpr int kMaxGemmProblems = 7;  // (a launch brings at most six; one may be cut in two)
 struct GemmBatch {
   GemmProblem p[kMaxGemmProblems];
   int count;

@@ -826,11 +826,17 @@ hipError_t enqueue_decoder(const map_decoder_weights& w, int B, const void* X, c
   if ((e = launch_rmsnorm(a, t.x1, w.ffn_norm, t.h, st)) != hipSuccess) return e;
   GemmBatch g2;
   memset(&g2, 0, sizeof(g2));
-  g2.p[0] = linear(t.h, R, w.w_gate_up, nullptr, t.gu, 2 * w.ff, w.d, EPI_BIAS);
+  g2.p[0] = linear(t.h, R, w.w_gate_up, nullptr, t.act, w.ff, w.d, EPI_SILU);
   g2.count = 1;
+  // SiLU(gate) * up in the product's epilogue, on its float32 sums (2944 rows,
+  // 2 x 11008 columns: 130 MB not written and not read again, @@SILU@@);
+  // weights that start off a 16-byte boundary run the register-staged
+  // kernel, which leaves both halves to silu_mul
+  const bool fused = gemm_direct_loads(MAP_BF16, g2);
+  if (!fused) g2.p[0] = linear(t.h, R, w.w_gate_up, nullptr, t.gu, 2 * w.ff, w.d, EPI_BIAS);
   gemm_finalize(g2);
   if ((e = launch_gemm(MAP_BF16, g2, "gemm_gate_up", st)) != hipSuccess) return e;
-  if ((e = launch_silu_mul(a, st)) != hipSuccess) return e;
+  if (!fused && (e = launch_silu_mul(a, st)) != hipSuccess) return e;
   return resid_product(t.act, R, w.w_down, w.d, w.ff, t.x1, Y, t.partial, cus, "gemm_down", st);
 }
 

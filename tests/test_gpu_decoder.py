@@ -134,3 +134,47 @@ def test_decoder_attention_block_edges(lens):
     want = oracle.decoder_layer(x, pos, seq_off, {k: bf16_bits_to_f32(v) for k, v in wb.items()}, H)
     row = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want - x, axis=1)
     assert row.max() <= 3e-2, (int(row.argmax()), float(row.max()))
+
+
+@pytest.mark.parametrize("lens", [
+    [500, 500, 409],            # products of 128-row tiles only, and of 192-row tiles with a last one of 65 rows
+    [512] * 5 + [451],          # 192-row tiles whose last one reaches into its lower half (131 rows)
+    [512] * 5 + [384],          # 256-row tiles, then 128 rows more; 192-row tiles, then 64 rows more
+    [512] * 9 + [392],          # 192-row tiles for the first rounds, 128-row tiles for the rest
+])
+def test_decoder_tile_heights(lens):
+    """Row counts whose products are cut into tiles of 256, 192 and 128 rows,
+    every row of the update held to the update's bar."""
+    d, H, ff = 1024, 8, 2816
+    announce(f"decoder tile heights, {sum(lens)} rows")
+    rng = np.random.default_rng(sum(lens))
+    seq_off = [0] + [int(v) for v in np.cumsum(lens)]
+    X = f32_to_bf16_bits(rng.standard_normal((seq_off[-1], d)).astype(np.float32))
+    pos = np.concatenate([np.arange(n) for n in lens]).astype(np.int32)
+    wb = _weights(d, ff, 12, std=0.03)
+    got = _run_and_check(X, pos, seq_off, wb, H, "tile heights")
+    x = bf16_bits_to_f32(X).astype(np.float64)
+    want = oracle.decoder_layer(x, pos, seq_off, {k: bf16_bits_to_f32(v) for k, v in wb.items()}, H)
+    row = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want - x, axis=1)
+    assert row.max() <= 3e-2, (int(row.argmax()), float(row.max()))
+
+
+def test_decoder_weights_off_alignment():
+    """Gate and up weights two bytes off a 16-byte boundary: the product by
+    the register-staged kernel and its separate SwiGLU."""
+    import paper_2608_06411_amd as mp
+    dev = device()
+    d, H, ff = 256, 2, 512
+    announce("decoder, gate and up weights off alignment")
+    rng = np.random.default_rng(13)
+    seq_off = [0, 70, 133]
+    x = _dev(f32_to_bf16_bits(rng.standard_normal((133, d)).astype(np.float32)), dev)
+    pos = torch.arange(133, dtype=torch.int32, device=dev)
+    wt = {k: _dev(v, dev) for k, v in _weights(d, ff, 14, std=0.05).items()}
+    want = mp.map_decoder_layer(mp.DecoderWeights(**wt, n_heads=H), x, pos, seq_off)
+    flat = torch.empty(2 * ff * d + 1, dtype=torch.bfloat16, device=dev)
+    flat[1:] = wt["w_gate_up"].reshape(-1)
+    wt["w_gate_up"] = flat[1:].view(2 * ff, d)
+    got = mp.map_decoder_layer(mp.DecoderWeights(**wt, n_heads=H), x, pos, seq_off)
+    du, dw = (got - x).double(), (want - x).double()
+    assert float((du - dw).norm() / dw.norm()) <= 1e-2  # two bf16 roundings more (2^-9 each) in one path
