@@ -167,7 +167,13 @@ struct Lds {
 // tokens' new rows (W) during the update; the two never live together.
 // mr2 holds the members' r^2 at the round start; the mkey space is not
 // read (the picking wave keeps the keys in registers).
-__host__ __device__ inline Lds lds_layout(int K, int G, int ch, int pcap, bool pipe) {
+// The kernel's variants: the own tokens brought up to date after the picks,
+// or during them with the coefficient rows of the pool's members and of the
+// own tokens in LDS, or during them with those rows in global memory.
+enum SelectMode : int { SEL_AFTER = 0, SEL_LDS = 1, SEL_GLOBAL = 2 };
+
+__host__ __device__ inline Lds lds_layout(int K, int G, int ch, int pcap, int mode) {
+  const bool pipe = mode != SEL_AFTER, cols = mode == SEL_LDS;
   Lds L;
   int o = 0;
   auto take = [&](int bytes) { const int r = o; o += (bytes + 15) & ~15; return r; };
@@ -186,21 +192,21 @@ __host__ __device__ inline Lds lds_layout(int K, int G, int ch, int pcap, bool p
   L.pslot = take(4 * pcap);
   L.pr = take(4 * pcap);
   L.pgain = take(4 * pcap);
-  // pipelined: the pool members' coefficient rows, and once the round's
-  // products are done this round's coefficients of the own tokens [ch][us];
-  // the non-pipelined variant reads the members' rows from global memory
-  L.pcol = take(4 * (pipe ? max(pcap * L.cs, ch * L.us) : 0));
+  // SEL_LDS: the pool members' coefficient rows, and once the round's products
+  // are done this round's coefficients of the own tokens [ch][us];
+  // SEL_GLOBAL: the latter only
+  L.pcol = take(4 * (cols ? max(pcap * L.cs, ch * L.us) : pipe ? ch * L.us : 0));
   L.U = take(4 * pcap * L.us);
   const int rbytes = 4 * pcap * L.rs, wbytes = 4 * pcap * L.ws;
   L.RW = take(rbytes > wbytes ? rbytes : wbytes);
   L.merge = take(max(8 * (G * kPub + 2), 4 * ch));  // also the picked-token flags
   L.bnd = take(8 * ((kPub + 1) * (NT / 64)));
   L.misc = take(64);
-  // pipelined update: the own tokens' coefficient rows of earlier rounds
-  // (token-major, stride 4 times an odd number), the earlier rounds' part of
-  // every pool member's row at the own tokens (D) and the stage counters
+  // SEL_LDS: the own tokens' coefficient rows of earlier rounds (token-major,
+  // stride 4 times an odd number); pipelined update: the earlier rounds' part
+  // of every pool member's row at the own tokens (D) and the stage counters
   L.ocs = ((K + 3) & ~3) + 4 + ((((K + 3) & ~3) / 4 + 1) % 2 == 0 ? 4 : 0);
-  L.ownC = pipe ? take(4 * ch * L.ocs) : 0;
+  L.ownC = cols ? take(4 * ch * L.ocs) : 0;
   L.D = pipe ? take(4 * pcap * L.ws) : 0;
   L.flags = pipe ? take(32) : 0;
   L.r2acc = pipe ? take(4 * 64) : 0;
@@ -782,8 +788,10 @@ __device__ __forceinline__ void gtile_product(const float* arow, const float* br
 
 // Global C is token-major: Ct[i][l] = c_{l,i}, rows of Kp floats (Kp = K
 // rounded up to 4), so one token's coefficients are contiguous.
-template <bool PIPE>
+template <int MODE>
 __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_begin) {
+  constexpr bool PIPE = MODE != SEL_AFTER;  // own tokens brought up to date during the picks
+  constexpr bool COLS = MODE == SEL_LDS;    // the coefficient rows that this needs are in LDS
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int G = a.G, ch = a.ch, pcap = a.pcap, K = a.K, K0 = a.K0, N = a.N;
   const int Kp = (K + 3) & ~3;
@@ -791,7 +799,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
   const bool skip = a.run_if && a.run_if[b] == 0;  // (uniform over the image's workgroups)
   if (skip && !a.gV) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const Lds L = lds_layout(K, G, ch, pcap, PIPE);
+  const Lds L = lds_layout(K, G, ch, pcap, MODE);
   int* midx = reinterpret_cast<int*>(lds + L.midx);
   float* mp = reinterpret_cast<float*>(lds + L.mp);
   float* mn = reinterpret_cast<float*>(lds + L.mn);
@@ -808,7 +816,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
   uint64_t* bndk = reinterpret_cast<uint64_t*>(lds + L.bnd);
   int* misc = reinterpret_cast<int*>(lds + L.misc);
   const int cs = L.cs, us = L.us, rs = L.rs, wsd = L.ws, ocs = L.ocs;
-  float* ownC = reinterpret_cast<float*>(lds + L.ownC);  // PIPE: [ch][ocs] own rows, earlier rounds
+  float* ownC = reinterpret_cast<float*>(lds + L.ownC);  // COLS: [ch][ocs] own rows, earlier rounds
   float* Dm = reinterpret_cast<float*>(lds + L.D);       // PIPE: [pcap][wsd] pool rows at the own tokens
   float* crow = pcol;                                    // PIPE, picks: [ch][us] this round's own rows
   int* npub = reinterpret_cast<int*>(lds + L.flags);     // PIPE: picks published this round
@@ -973,7 +981,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
     // are used only when the flag is set)
     const int K0q = (K0 + 3) >> 2;
     float4 rows[8];
-    if (PIPE) {  // piece e = (own token e >> 5, float4 e & 31): at most 64 x 32
+    if (COLS) {  // piece e = (own token e >> 5, float4 e & 31): at most 64 x 32
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const int e = tid + NT * u, i = min(e >> 5, cnt - 1), q = min(e & 31, K0q - 1);
@@ -991,7 +999,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
         if (r2v != r2v) my_state = 2;  // NaN: a member of R0
         else my_r2 = r2v;
       }
-      if (PIPE) {
+      if (COLS) {
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const int e = tid + NT * u, i = e >> 5, q = e & 31;
@@ -1093,15 +1101,15 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
       for (int q = 0; q < NT / 64; ++q) beta = bndk[NT / 64 + q] > beta ? bndk[NT / 64 + q] : beta;
     }
     __syncthreads();
-    // members: state, their block of S and (pipelined variant) their
-    // columns (rows < t, written by their owners before the barrier; the
-    // other variant reads them from global memory where it needs them).
+    // members: state, their block of S and (SEL_LDS) their columns (rows < t,
+    // written by their owners before the barrier; the other variants read
+    // them from global memory where they need them).
     // Every global load of a thread is issued, at clamped (valid) addresses,
     // before its first LDS store, so the phase costs about one memory round
     // trip.
     if (pn > 0) {
       constexpr int CB = 12;  // column pieces per thread per batch
-      // pipelined: member (tid >> 2) is loaded by four threads, float4 pieces
+      // COLS: member (tid >> 2) is loaded by four threads, float4 pieces
       // q = (tid & 3) + 4 u; pieces up to column tk = t rounded up to 8 are
       // written, with the columns at or past t set to zero (the round-start
       // product then needs no masks)
@@ -1113,7 +1121,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
       const int mq = tid >> 2;
       const float* csrc = Ct + (long long)midx[min(mq, pn - 1)] * Kp;
       f32x4_t cv[CB];
-      if (PIPE)
+      if (COLS)
 #pragma unroll
         for (int u = 0; u < CB; ++u)
           cv[u] = *reinterpret_cast<const f32x4_t*>(csrc + 4 * min((tid & 3) + 4 * u, max(tq - 1, 0)));
@@ -1137,7 +1145,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
         mqn[tid] = pc * ni;
         mr2[tid] = t == 0 ? (ni > 0.0f ? 1.0f : 0.0f) : r2m;
       }
-      if (PIPE && mq < pn) {
+      if (COLS && mq < pn) {
         auto put = [&](int q, f32x4_t v) {  // piece q, zero at and past column t
           const int l = 4 * q;
           v.x = l < t ? v.x : 0.0f;
@@ -1154,7 +1162,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
         for (int q = (tid & 3) + 4 * CB; q < tk4; q += 4)  // long columns: the rest
           put(q, *reinterpret_cast<const f32x4_t*>(csrc + 4 * min(q, tq - 1)));
       }
-      if (PIPE && t > 0)  // the own rows' columns t .. tk - 1 are zero too
+      if (COLS && t > 0)  // the own rows' columns t .. tk - 1 are zero too
         for (int e = tid; e < cnt * 8; e += NT) {
           const int i = e >> 3, l = t + (e & 7);
           if (l < 4 * tk4) ownC[i * ocs + l] = 0.0f;
@@ -1189,7 +1197,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
       for (int e = 0; e < 16; ++e)
         cur[e] = Rm[min(32 * tr + 8 * (e >> 2) + 4 * h + (e & 3), pn - 1) * rs + min(32 * tc + r, pn - 1)];
       f32x16_t acc;
-      if (PIPE) {
+      if (COLS) {
         tile_product(pcol + min(32 * tr + r, pn - 1) * cs + 4 * h, pcol + min(32 * tc + r, pn - 1) * cs + 4 * h,
                      (t + 7) & ~7, acc);
       } else {  // the members' rows in global C (written before the last image barrier)
@@ -1345,7 +1353,10 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
           f32x16_t acc;
 #pragma unroll
           for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
-          if (t0 > 0)
+          if (!COLS)
+            gtile_product<4>(Ct + (long long)midx[min(32 * ti + r, pn - 1)] * Kp,
+                             Ct + (long long)(c0 + min(32 * tj + r, cnt - 1)) * Kp, t0, Kp, h, acc);
+          else if (t0 > 0)
             tile_product(pcol + min(32 * ti + r, pn - 1) * cs + 4 * h, ownC + min(32 * tj + r, cnt - 1) * ocs + 4 * h,
                          (t0 + 7) & ~7, acc);
 #pragma unroll
@@ -1408,7 +1419,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
           const float c = v * rk;  // rk = 1 / r_k, zero when the pick adds no basis vector
           cr[k] = c;
           // the finished row goes straight to the own rows in LDS and to C
-          ownC[lane * ocs + t0 + k] = c;
+          if (COLS) ownC[lane * ocs + t0 + k] = c;
           if (lane < cnt) Ct[(long long)(c0 + lane) * Kp + t0 + k] = c;
           csq = fmaf(c, c, csq);
           ++k;
@@ -1687,39 +1698,42 @@ hipError_t launch_select_clear(const SelectArgs& a, hipStream_t s) {
 hipError_t launch_select(SelectArgs& a, hipStream_t s) {
   const int K = a.K, N = a.N;
   constexpr int kMaxLds = 160 * 1024;
-  constexpr int kMinPipePool = 48;  // below this the pipelined variant loses more to extra rounds
+  constexpr int kMinLdsPool = 48;  // below this SEL_LDS loses more to extra rounds
   const int cus = device_info().cus > 0 ? device_info().cus : 1;
   int chosen_ch = 0, chosen_pcap = 0, chosen_G = 0, chosen_bytes = 0, per_cu = 0;
-  bool chosen_pipe = false;
+  int chosen_mode = SEL_AFTER;
   for (int ch : {64, 128, 256}) {
     const int G = (N + ch - 1) / ch;
     if (G > 128) continue;
-    bool pipe = ch == 64;
+    // The update runs during the picks when 64 own tokens are one per lane of
+    // its wave, with the rows it needs in LDS while a pool of kMinLdsPool fits
+    // beside them (K up to about 260), else with the rows in global memory
+    // @@SEL@@
+    int mode = ch == 64 ? SEL_LDS : SEL_AFTER;
     int pcap = kMaxPool;
-    while (pcap > 8 && lds_layout(K, G, ch, pcap, pipe).bytes > kMaxLds) pcap -= 8;
-    if (pipe && pcap < kMinPipePool) {
-      pipe = false;
+    while (pcap > 8 && lds_layout(K, G, ch, pcap, mode).bytes > kMaxLds) pcap -= 8;
+    if (mode == SEL_LDS && pcap < kMinLdsPool) {
+      mode = SEL_GLOBAL;
       pcap = kMaxPool;
-      while (pcap > 8 && lds_layout(K, G, ch, pcap, false).bytes > kMaxLds) pcap -= 8;
     }
-    const int bytes = lds_layout(K, G, ch, pcap, pipe).bytes;
+    const int bytes = lds_layout(K, G, ch, pcap, mode).bytes;
     if (bytes > kMaxLds) continue;
-    const void* fn = pipe ? reinterpret_cast<const void*>(select_kernel<true>)
-                          : reinterpret_cast<const void*>(select_kernel<false>);
+    const auto fn = mode == SEL_LDS      ? select_kernel<SEL_LDS>
+                    : mode == SEL_GLOBAL ? select_kernel<SEL_GLOBAL>
+                                         : select_kernel<SEL_AFTER>;
     if (bytes > 65536) {
-      hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
       if (e != hipSuccess) return e;
     }
     int pc = 0;
-    hipError_t e = pipe ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&pc, select_kernel<true>, NT, bytes)
-                        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&pc, select_kernel<false>, NT, bytes);
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&pc, fn, NT, bytes);
     if (e != hipSuccess) return e;
     if (pc <= 0) continue;
     chosen_ch = ch;
     chosen_pcap = pcap;
     chosen_G = G;
     chosen_bytes = bytes;
-    chosen_pipe = pipe;
+    chosen_mode = mode;
     per_cu = pc;
     if ((long long)a.B * G <= (long long)pc * cus) break;  // every image at once
   }
@@ -1728,7 +1742,7 @@ hipError_t launch_select(SelectArgs& a, hipStream_t s) {
   a.G = chosen_G;
   a.pcap = chosen_pcap;
   if (a.gV) {  // the order must fit where the pool's Gram matrix was
-    const Lds L = lds_layout(K, chosen_G, chosen_ch, chosen_pcap, chosen_pipe);
+    const Lds L = lds_layout(K, chosen_G, chosen_ch, chosen_pcap, chosen_mode);
     const int rw = 4 * chosen_pcap * (L.rs > L.ws ? L.rs : L.ws);
     if (4 * ((K + 7) & ~7) > rw || (a.row_bytes & 15) != 0) a.gV = nullptr;
   }
@@ -1750,13 +1764,11 @@ hipError_t launch_select(SelectArgs& a, hipStream_t s) {
   }
   for (int b0 = 0; b0 < a.B; b0 += per_launch) {
     const int nb = a.B - b0 < per_launch ? a.B - b0 : per_launch;
-    const hipError_t e =
-        chosen_pipe ? launch_kernel(a.fallback ? "select_full" : a.tier2 ? "select_t2" : "select", select_kernel<true>,
-                                    dim3(nb * chosen_G),
-                                    dim3(NT), static_cast<size_t>(chosen_bytes), s, a, b0)
-                    : launch_kernel(a.fallback ? "select_full" : a.tier2 ? "select_t2" : "select", select_kernel<false>,
-                                    dim3(nb * chosen_G),
-                                    dim3(NT), static_cast<size_t>(chosen_bytes), s, a, b0);
+    const auto fn = chosen_mode == SEL_LDS      ? select_kernel<SEL_LDS>
+                    : chosen_mode == SEL_GLOBAL ? select_kernel<SEL_GLOBAL>
+                                                : select_kernel<SEL_AFTER>;
+    const hipError_t e = launch_kernel(a.fallback ? "select_full" : a.tier2 ? "select_t2" : "select", fn,
+                                       dim3(nb * chosen_G), dim3(NT), static_cast<size_t>(chosen_bytes), s, a, b0);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
