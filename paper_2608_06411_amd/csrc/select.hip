@@ -158,7 +158,7 @@ __host__ __device__ inline int col_stride(int K) { return ((K + 31) & ~31) + 4; 
 struct Lds {
   // byte offsets into the dynamic LDS block
   int midx, mp, mn, mqn, mr2, mkey, pslot, pr, pgain, pcol, U, RW, merge, bnd, misc;
-  int ownC, D, flags, r2acc;  // pipelined update only
+  int ownC, D, D3, flags, r2acc;  // pipelined update only
   int bytes;
   int cs, us, rs, ws, ocs;
 };
@@ -208,6 +208,7 @@ __host__ __device__ inline Lds lds_layout(int K, int G, int ch, int pcap, int mo
   L.ocs = ((K + 3) & ~3) + 4 + ((((K + 3) & ~3) / 4 + 1) % 2 == 0 ? 4 : 0);
   L.ownC = cols ? take(4 * ch * L.ocs) : 0;
   L.D = pipe ? take(4 * pcap * L.ws) : 0;
+  L.D3 = mode == SEL_GLOBAL ? take(3 * 4 * 32 * 32) : 0;  // the last tile's three ranges of earlier rows
   L.flags = pipe ? take(32) : 0;
   L.r2acc = pipe ? take(4 * 64) : 0;
   L.bytes = o;
@@ -818,6 +819,7 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
   const int cs = L.cs, us = L.us, rs = L.rs, wsd = L.ws, ocs = L.ocs;
   float* ownC = reinterpret_cast<float*>(lds + L.ownC);  // COLS: [ch][ocs] own rows, earlier rounds
   float* Dm = reinterpret_cast<float*>(lds + L.D);       // PIPE: [pcap][wsd] pool rows at the own tokens
+  float* D3 = reinterpret_cast<float*>(lds + L.D3);      // SEL_GLOBAL: [3][32][32]
   float* crow = pcol;                                    // PIPE, picks: [ch][us] this round's own rows
   int* npub = reinterpret_cast<int*>(lds + L.flags);     // PIPE: picks published this round
   int* pdone = npub + 3;                                 // round tag once the picks are over
@@ -1343,7 +1345,10 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
       // pick order, c_{k,i} = (W[pick_k][i] - sum_{k'<k} U[pick_k][k'] c_{k',i}) / r_k.
       if (pn > 0) {
         const int r = lane & 31, h = lane >> 5;
-        for (int q = wave == 1 ? 0 : wave == 3 ? 1 : 2; q < (wave == 2 ? 4 : (wave == 1 ? 1 : 2)); ++q) {
+        // SEL_GLOBAL: the fourth tile's sum over the earlier rows in three
+        // ranges, one per wave (two tiles on one wave would finish last)
+        const int v = wave == 1 ? 0 : wave == 3 ? 1 : 2;
+        for (int q = v; q < (COLS && v == 2 ? 4 : v + 1); ++q) {
           const int ti = q >> 1, tj = q & 1;
           const int col = c0 + min(32 * tj + r, cnt - 1);
           float sv[16];
@@ -1365,10 +1370,33 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
             if (m < pn) Dm[m * wsd + 32 * tj + r] = sv[e] - acc[e];
           }
         }
+        if (!COLS && pn > 32 && cnt > 32) {
+          const int third = 8 * ((((t0 + 7) >> 3) + 2) / 3), lo = min(v * third, t0), hi = min(lo + third, t0);
+          f32x16_t acc;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+          if (hi > lo)
+            gtile_product<4>(Ct + (long long)midx[min(32 + r, pn - 1)] * Kp + lo,
+                             Ct + (long long)(c0 + min(32 + r, cnt - 1)) * Kp + lo, hi - lo, Kp - lo, h, acc);
+#pragma unroll
+          for (int e = 0; e < 16; ++e) D3[(v * 32 + 8 * (e >> 2) + 4 * h + (e & 3)) * 32 + r] = acc[e];
+        }
       }
       if (lane == 0) __hip_atomic_fetch_add(dready, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);  // once per wave
       if (wave == 1) {
         while (__hip_atomic_load(dready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < 3) __builtin_amdgcn_s_sleep(1);
+        if (!COLS && pn > 32 && cnt > 32) {  // the fourth tile: the entries of S less the three ranges' sums
+          const int r = lane & 31, h = lane >> 5, col = c0 + min(32 + r, cnt - 1);
+          float sv[16];
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            sv[e] = S[(long long)midx[min(32 + 8 * (e >> 2) + 4 * h + (e & 3), pn - 1)] * N + col];
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int m = 8 * (e >> 2) + 4 * h + (e & 3), at = m * 32 + r;
+            if (32 + m < pn) Dm[(32 + m) * wsd + 32 + r] = sv[e] - ((D3[at] + D3[1024 + at]) + D3[2048 + at]);
+          }
+        }
         float* cr = crow + lane * us;  // this round's own row: zero past the finished entries
         for (int e = 0; e < us / 4; ++e) reinterpret_cast<float4*>(cr)[e] = make_float4(0.f, 0.f, 0.f, 0.f);
         // The finisher stops once the picks are over and it has handled every
@@ -1397,24 +1425,27 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
           const float* ur = U + sk * us;
           const float rk = prr[k];
           const float w0 = Dm[sk * wsd + lane];
-          // all reads first (one LDS round trip), products only for the
-          // groups of 16 rows finished so far
-          float4 u4[kMaxPool / 4], c4[kMaxPool / 4];
-#pragma unroll
-          for (int j = 0; j < kMaxPool / 4; ++j) {
-            u4[j] = *reinterpret_cast<const float4*>(ur + 4 * j);
-            c4[j] = *reinterpret_cast<const float4*>(cr + 4 * j);
-          }
+          // all reads first (one LDS round trip), reads and products only
+          // for the groups of 16 rows finished so far
           float e4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+          auto dot = [&](auto ngc) {
+            constexpr int NG = decltype(ngc)::value;
+            float4 u4[4 * NG], c4[4 * NG];
 #pragma unroll
-          for (int g = 0; g < kMaxPool / 16; ++g) {
-            if (16 * g >= k) break;
+            for (int j = 0; j < 4 * NG; ++j) {
+              u4[j] = *reinterpret_cast<const float4*>(ur + 4 * j);
+              c4[j] = *reinterpret_cast<const float4*>(cr + 4 * j);
+            }
 #pragma unroll
-            for (int j = 4 * g; j < 4 * g + 4; ++j) {
+            for (int j = 0; j < 4 * NG; ++j) {
               e4[0] = fmaf(u4[j].x, c4[j].x, e4[0]); e4[1] = fmaf(u4[j].y, c4[j].y, e4[1]);
               e4[2] = fmaf(u4[j].z, c4[j].z, e4[2]); e4[3] = fmaf(u4[j].w, c4[j].w, e4[3]);
             }
-          }
+          };
+          if (k > 48) dot(IntC<4>{});
+          else if (k > 32) dot(IntC<3>{});
+          else if (k > 16) dot(IntC<2>{});
+          else if (k > 0) dot(IntC<1>{});
           const float v = w0 - ((e4[0] + e4[1]) + (e4[2] + e4[3]));
           const float c = v * rk;  // rk = 1 / r_k, zero when the pick adds no basis vector
           cr[k] = c;

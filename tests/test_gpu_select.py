@@ -127,3 +127,16 @@ def test_select_r0_candidate_overflow():
     want = np.lexsort((i, -p[0].astype(np.float64)))[:K0]
     np.testing.assert_array_equal(order[0][:K0], want)
     _check(V, p, K, K0, idx, order, gain)
+
+
+@pytest.mark.parametrize("N,K,K0", [(641, 300, 0), (672, 300, 40), (673, 400, 200), (64, 64, 0), (700, 321, 320), (703, 640, 100)])
+def test_select_rows_in_global_memory(N, K, K0):
+    """K past what the own tokens' rows and the pool's fit in LDS for: a last
+    workgroup of 1, 32, 33 or 63 tokens, a number of earlier rows that is no
+    multiple of eight, R0 by pool rounds, and a rank that runs out (D < K)."""
+    announce(f"select, rows in global memory N={N} K={K} K0={K0}")
+    D = 128 if K > 600 else 512
+    V, store = _tokens(N + K0, 1, N, D, "bf16", clusters=N // 2)
+    p = peaked_scores(1, N, seed=N + K0)
+    idx, order, gain = _select(store, "bf16", p, K, K0)
+    _check(V, p, K, K0, idx, order, gain)
