@@ -881,83 +881,97 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
 }
 
 // ------------------------------------------------------------ float32 tiles
-// float32 products: 64 x 64 tiles, eight waves in two groups of four; in a
-// group each wave forms one 32 x 32 block (v_mfma_f32_32x32x2_f32), group g
-// over the K slices of 32 with kt % 2 = g, and the two sums are added in LDS
-// at the end.  The slices come by direct loads through a ring of four pairs
-// (32 KiB each).  The float32 matrix rate bounds it (a slice's products take
-// 1024 clocks on each SIMD, its operand reads 256 of LDS), so small tiles
-// cost nothing and fill the chip, and two waves per SIMD hide the reads and
-// the barriers of each other.
-// A 576 x 1024 x 4096 layer with its 576-token Gram matrix and the folds: 336
-// us on 128 x 128 tiles, 79 of them for 256 compute units, now about 75;
-// 4096 x 4096 x 4096 1.21 ms (113 TFLOP/s of about 150 that products on
-// registers alone reach).
-// Requirements (checked by the host): K % 32 == 0, lda and ldb multiples of
-// 4, A and B 16-byte aligned, no RoPE epilogue, K range or index map.
-constexpr int kF32 = 64;
-constexpr int kF32Pairs = 4;
-constexpr int kF32Threads = 512;
+// 64 x 64 tiles for float32, and for bf16 launches too small to fill the chip
+// with larger ones: eight waves in two groups of four; in a group each wave
+// forms one 32 x 32 block, group g over the 128-byte K slices (32 floats, 64
+// bf16) with kt % 2 = g, and the two sums are added in LDS at the end.  The
+// slices come by direct loads through a ring of four pairs (32 KiB each).
+// float32: the matrix rate bounds it (a slice's products take 1024 clocks on
+// each SIMD, its operand reads 256 of LDS), so small tiles cost nothing and
+// fill the chip, and two waves per SIMD hide the reads and the barriers of
+// each other.  A 576 x 1024 x 4096 layer with its 576-token Gram matrix and
+// the folds: 336 us on 128 x 128 tiles, 79 of them for 256 compute units, now
+// about 75; 4096 x 4096 x 4096 1.21 ms (113 TFLOP/s of about 150 that products
+// on registers alone reach).
+// bf16: a compute unit takes in about 50 GB/s with the loads that LDS has
+// room for in flight, so a tile's time is its operand bytes, half those of a
+// 128 x 128 tile: @@SMALL@@
+// Requirements (checked by the host): K a multiple of the slice, lda and ldb
+// multiples of 16 bytes, A and B 16-byte aligned, no RoPE or SwiGLU
+// epilogue, K range or index map.
+constexpr int kTile = 64;
+constexpr int kTilePairs = 4;
+constexpr int kTileThreads = 512;
 
-__global__ __launch_bounds__(kF32Threads) void gemm_f32_kernel(const GemmBatch args) {
-  __shared__ uint4 st[kF32Pairs][2][2][kF32][8];  // per pair: slice of group 0, of group 1; each A rows, B rows
+template <typename T>
+__global__ __launch_bounds__(kTileThreads) void gemm_tile64_kernel(const GemmBatch args) {
+  constexpr int BK = Slice<T>::BK, VEC = Slice<T>::VEC;
+  __shared__ uint4 st[kTilePairs][2][2][kTile][8];  // per pair: slice of group 0, of group 1; each A rows, B rows
   int pi, bt, tm, tn, kc, local;
   decode_tile(args, pi, bt, tm, tn, kc, local);
   const GemmProblem& P = args.p[pi];
   if (P.run_if && P.run_if[bt] == 0) return;
-  const int M = P.M, N = P.N, m0 = tm * kF32, n0 = tn * kF32, nk = P.K / 32;
-  const float* __restrict__ A = static_cast<const float*>(P.A) + bt * P.strideA;
-  const float* __restrict__ B = static_cast<const float*>(P.B) + bt * P.strideB;
+  const int M = P.M, N = P.N, m0 = tm * kTile, n0 = tn * kTile, nk = P.K / BK;
+  const T* __restrict__ A = static_cast<const T*>(P.A) + bt * P.strideA;
+  const T* __restrict__ B = static_cast<const T*>(P.B) + bt * P.strideB;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave >> 2, w4 = wave & 3, wm = w4 >> 1, wn = w4 & 1, lr = lane & 31, lh = lane >> 5;
   const int np = (nk + 1) / 2, own = (nk - grp + 1) / 2;  // pairs; this group's slices
   // wave w of a group moves rows 16 w .. 16 w + 15 of A and of B of its
   // group's slices, one instruction per 8 rows (rows past the matrix read
   // its last row; they are never stored)
-  const float* ga[2];
-  const float* gb[2];
+  const T* ga[2];
+  const T* gb[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int r = 16 * w4 + 8 * j + (lane >> 3), v = (lane & 7) ^ swz(r);
-    ga[j] = A + (long long)min(m0 + r, M - 1) * P.lda + 4 * v + 32 * grp;
-    gb[j] = B + (long long)min(n0 + r, N - 1) * P.ldb + 4 * v + 32 * grp;
+    ga[j] = A + (long long)min(m0 + r, M - 1) * P.lda + VEC * v + BK * grp;
+    gb[j] = B + (long long)min(n0 + r, N - 1) * P.ldb + VEC * v + BK * grp;
   }
-  const uint32_t wrow = lds_addr(&st[0][0][0][0][0]) + static_cast<uint32_t>(grp) * (2u * kF32 * 128u) +
+  const uint32_t wrow = lds_addr(&st[0][0][0][0][0]) + static_cast<uint32_t>(grp) * (2u * kTile * 128u) +
                         static_cast<uint32_t>(w4) * 16u * 128u;
   auto issue = [&](int p) {
-    const uint32_t m = wrow + static_cast<uint32_t>(p % kF32Pairs) * (4u * kF32 * 128u);
+    const uint32_t m = wrow + static_cast<uint32_t>(p % kTilePairs) * (4u * kTile * 128u);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      dma16(ga[j] + 64 * p, m + 1024u * j);
-      dma16(gb[j] + 64 * p, m + kF32 * 128u + 1024u * j);
+      dma16(ga[j] + 2 * BK * p, m + 1024u * j);
+      dma16(gb[j] + 2 * BK * p, m + kTile * 128u + 1024u * j);
     }
   };
   f32x16_t acc[1][1];
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.0f;
-  for (int p = 0; p < min(kF32Pairs - 1, own); ++p) issue(p);
+  for (int p = 0; p < min(kTilePairs - 1, own); ++p) issue(p);
   for (int p = 0; p < np; ++p) {
     // this wave's part of its group's slice p (past its last one: nothing is outstanding)
-    wait_vm_lgkm0(4 * max(0, min(kF32Pairs - 2, own - 1 - p)));
+    wait_vm_lgkm0(4 * max(0, min(kTilePairs - 2, own - 1 - p)));
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();  // every wave's part, and every wave is done with pair p - 1
     asm volatile("" ::: "memory");
-    if (p + kF32Pairs - 1 < own) issue(p + kF32Pairs - 1);
+    if (p + kTilePairs - 1 < own) issue(p + kTilePairs - 1);
     if (p >= own) break;  // (the last pair of an odd count: group 1 has no slice)
-    const uint4 (*As)[8] = st[p % kF32Pairs][grp][0];
-    const uint4 (*Bs)[8] = st[p % kF32Pairs][grp][1];
-    float4 a[4], b[4];
+    const uint4 (*As)[8] = st[p % kTilePairs][grp][0];
+    const uint4 (*Bs)[8] = st[p % kTilePairs][grp][1];
+    uint4 a[4], b[4];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {  // lane half lh covers k = 16 lh + 4 g + (0..3)
-      const int v = (4 * lh + g) ^ swz(lr);
-      a[g] = __builtin_bit_cast(float4, As[32 * wm + lr][v]);
-      b[g] = __builtin_bit_cast(float4, Bs[32 * wn + lr][v]);
+    for (int g = 0; g < 4; ++g) {
+      // float32: lane half lh covers k = 16 lh + 4 g + (0..3); bf16: 16 g + 8 lh + (0..7)
+      const int v = (sizeof(T) == 4 ? 4 * lh + g : 2 * g + lh) ^ swz(lr);
+      a[g] = As[32 * wm + lr][v];
+      b[g] = Bs[32 * wn + lr][v];
     }
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int g = 0; g < 4; ++g) {
+      if constexpr (sizeof(T) == 4) {
+        const float4 af = __builtin_bit_cast(float4, a[g]), bf = __builtin_bit_cast(float4, b[g]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g][e], b[g][e], acc[0][0], 0, 0, 0);
+        for (int e = 0; e < 4; ++e)
+          acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[e], bf[e], acc[0][0], 0, 0, 0);
+      } else {
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a[g]),
+                                                            __builtin_bit_cast(bf16x8_t, b[g]), acc[0][0], 0, 0, 0);
+      }
+    }
   }
   __syncthreads();  // the ring is read out: group 1's sums pass through it
   float* sums = reinterpret_cast<float*>(&st[0][0][0][0][0]) + w4 * 16 * 64 + lane;
@@ -969,7 +983,7 @@ __global__ __launch_bounds__(kF32Threads) void gemm_f32_kernel(const GemmBatch a
   if (grp) return;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[0][0][r] += sums[64 * r];
-  epilogue<float, 1, 1>(P, bt, tm, tn, acc, nullptr, nullptr, tid, lane, wm, wn);
+  epilogue<T, 1, 1>(P, bt, tm, tn, acc, nullptr, nullptr, tid, lane, wm, wn);
 }
 
 // ------------------------------------------------------------ 256 x 256 tiles
@@ -1820,16 +1834,30 @@ static bool big_tiles_pay(const GemmBatch& g, GemmBatch& q, int& tm) {
   return big >= 0 && big < small_tiles_cost(g);
 }
 
-// Whether a float32 launch meets the float32 tiles' requirements.
-static bool f32_tiles_fit(const GemmBatch& g) {
+// Whether a launch meets the 64 x 64 tiles' requirements.
+static bool tile64_fits(const GemmBatch& g, int vec, int bk) {
+  if (g.norm_blocks || g.norm_tiles) return false;
   for (int i = 0; i < g.count; ++i) {
     const GemmProblem& p = g.p[i];
-    if (p.epi == EPI_ROPE || p.epi == EPI_PARTIAL || p.ksplit > 1 || p.mapA || p.mapB || p.K % 32 != 0 ||
-        p.lda % 4 != 0 || p.ldb % 4 != 0 || p.strideA % 4 != 0 || p.strideB % 4 != 0 ||
+    if (p.epi == EPI_ROPE || p.epi == EPI_PARTIAL || p.epi == EPI_SILU || p.ksplit > 1 || p.mapA || p.mapB ||
+        p.K % bk != 0 || p.lda % vec != 0 || p.ldb % vec != 0 || p.strideA % vec != 0 || p.strideB % vec != 0 ||
         (reinterpret_cast<uintptr_t>(p.A) & 15) != 0 || (reinterpret_cast<uintptr_t>(p.B) & 15) != 0)
       return false;
   }
   return true;
+}
+
+// 64 x 64 tiles for a bf16 launch when one round of workgroups holds all of
+// its long ones: a round then takes half as long as one of 128 x 128 tiles;
+// two rounds would take as long.
+static bool tile64_pays(const GemmBatch& g) {
+  long long n = 0;
+  for (int i = 0; i < g.count; ++i) {
+    const GemmProblem& p = g.p[i];
+    const long long a = (p.M + kTile - 1) / kTile, b = (p.N + kTile - 1) / kTile;
+    if (i == 0 || 2 * p.K > g.p[0].K) n += (p.triangular ? a * (a + 1) / 2 : a * b) * p.batch;
+  }
+  return n <= gemm_cus();
 }
 
 bool gemm_big_tiles(map_dtype dt, const GemmBatch& g) {
@@ -1849,6 +1877,10 @@ hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipSt
     if (dma && big_tiles_pay(g, q, tm))
       return launch_kernel(name, g.norm_tiles ? gemm_big_kernel<true, 256> : tm == 192 ? gemm_big_kernel<false, 192> : gemm_big_kernel<false, 256>,
                            dim3(q.total_tiles), dim3(kBigThreads), 0, s, q);
+    if (dma && tile64_fits(g, 8, 64) && tile64_pays(g)) {
+      finalize_tiles(q = g, kTile);
+      return launch_kernel(name, gemm_tile64_kernel<bf16_t>, dim3(q.total_tiles), dim3(kTileThreads), 0, s, q);
+    }
     if (dma)
       return launch_kernel(name, gemm_dma_kernel, dim3(g.total_tiles + g.norm_blocks), dim3(kDmaThreads), 0, s, g);
     if (g.norm_blocks) return hipErrorInvalidValue;
@@ -1856,10 +1888,10 @@ hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipSt
       if (g.p[i].epi == EPI_PARTIAL || g.p[i].epi == EPI_SILU || g.p[i].mapA || g.p[i].mapB) return hipErrorInvalidValue;
     return launch_kernel(name, gemm_kernel<bf16_t>, dim3(g.total_tiles), dim3(NT), 0, s, g);
   }
-  if (f32_tiles_fit(g)) {
+  if (tile64_fits(g, 4, 32)) {
     GemmBatch q = g;
-    finalize_tiles(q, kF32);
-    return launch_kernel(name, gemm_f32_kernel, dim3(q.total_tiles), dim3(kF32Threads), 0, s, q);
+    finalize_tiles(q, kTile);
+    return launch_kernel(name, gemm_tile64_kernel<float>, dim3(q.total_tiles), dim3(kTileThreads), 0, s, q);
   }
   return launch_kernel(name, gemm_kernel<float>, dim3(g.total_tiles), dim3(NT), 0, s, g);
 }

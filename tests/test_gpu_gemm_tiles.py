@@ -75,3 +75,21 @@ def test_f32_tiles_cosine(B, N, D):
     for b in range(B):
         assert float((S[b].double() - v[b] @ v[b].t()).abs().max()) < 1e-5
         assert torch.equal(S[b], S[b].t())
+
+
+# bf16 launches on 64 x 64 tiles: four slices only (fewer than the ring
+# holds), one row past a tile, several images, and one tile too many for one
+# round of workgroups (128 x 128 tiles)
+@pytest.mark.parametrize("B,N,D", [(1, 65, 256), (3, 33, 512), (2, 128, 768), (1, 1408, 256), (1, 1409, 256)])
+def test_small_bf16_tiles_cosine(B, N, D):
+    from paper_2608_06411_amd import map_similarity
+    dev = device()
+    announce(f"64 x 64 bf16 tiles, cosine B={B} N={N} D={D}")
+    g = torch.Generator(device=dev)
+    g.manual_seed(N + D)
+    V = torch.randn(B, N, D, generator=g, device=dev).to(torch.bfloat16)
+    S, norms = map_similarity(V)
+    v = V.double() / V.double().norm(dim=2, keepdim=True)
+    for b in range(B):
+        assert float((S[b].double() - v[b] @ v[b].t()).abs().max()) < 1e-5
+        assert torch.equal(S[b], S[b].t())
