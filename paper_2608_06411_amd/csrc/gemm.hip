@@ -1044,7 +1044,12 @@ __device__ __forceinline__ void phase_barrier() {
 //       32 wm + (0..31)), the last two phases have half the products;
 //   128 rows or fewer in a tile: two phases a slice (no lower half), the
 //       slices in a ring of three.
-// @@COST@@
+// The rule (plan_big) counts a tile as its share of the products (0.75, 0.5)
+// plus its start and epilogue.  2944 x 4096 x 4096: 192 tiles of 256 rows on
+// 256 units 107 us, 256 tiles of 192 rows 96; 2944 x 12288 x 4096: 576 tiles
+// 292 us, 768 of 192 rows 260; 36864 x 1024 x 3584 with its question rows
+// and folds: 596 tiles (2.3 rounds) 320 us, 512 and 160 of 128 rows 287;
+// 5760 x 1024 x 4096: 128 x 128 tiles 92 us, 180 of 128 x 256 74.
 //
 // NORMS: the launch has row norms to form (GemmProblem::norm_at).
 template <bool NORMS, int TM>
@@ -1866,6 +1871,10 @@ bool gemm_big_tiles(map_dtype dt, const GemmBatch& g) {
   return gemm_direct_loads(dt, g) && big_tiles_pay(g, q, tm);
 }
 
+bool gemm_small_tiles(map_dtype dt, const GemmBatch& g) {
+  return gemm_direct_loads(dt, g) && !gemm_big_tiles(dt, g) && tile64_fits(g, 8, 64) && tile64_pays(g);
+}
+
 hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipStream_t s) {
   if (g.total_tiles == 0) return hipSuccess;
   // the in-tile row norms exist in the 256 x 256 kernel only
@@ -1878,7 +1887,8 @@ hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipSt
       return launch_kernel(name, g.norm_tiles ? gemm_big_kernel<true, 256> : tm == 192 ? gemm_big_kernel<false, 192> : gemm_big_kernel<false, 256>,
                            dim3(q.total_tiles), dim3(kBigThreads), 0, s, q);
     if (dma && tile64_fits(g, 8, 64) && tile64_pays(g)) {
-      finalize_tiles(q = g, kTile);
+      q = g;
+      finalize_tiles(q, kTile);
       return launch_kernel(name, gemm_tile64_kernel<bf16_t>, dim3(q.total_tiles), dim3(kTileThreads), 0, s, q);
     }
     if (dma)

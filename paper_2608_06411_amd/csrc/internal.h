@@ -138,6 +138,7 @@ struct GemmBatch {
 void gemm_finalize(GemmBatch& g);  // computes the tile counts
 bool gemm_direct_loads(map_dtype dt, const GemmBatch& g);  // launch_gemm would use the direct-load kernel
 bool gemm_big_tiles(map_dtype dt, const GemmBatch& g);     // ... with 256 x 256 tiles
+bool gemm_small_tiles(map_dtype dt, const GemmBatch& g);   // ... with 64 x 64 tiles
 hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipStream_t s);
 // The projection with the RoPE epilogue (every problem EPI_ROPE, at most two):
 // a K-split kernel for bf16 and N <= 128, else launch_gemm.

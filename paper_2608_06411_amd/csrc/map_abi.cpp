@@ -333,15 +333,17 @@ hipError_t enqueue_score(const map_weights& w, map_dtype dt, int B, int N, const
   g1.p[g1.count++] = linear(w.w_q, w.d_p, s.w2t_t, nullptr, s.wc_t, w.D_h, w.D_h, EPI_BIAS);  // W_Q W2
   gemm_finalize(g1);
   // The row norms: by prep, or (norms_in_layer1) inside the layer-1 launch:
-  // with 256 x 256 tiles, by the first column of f_V's tiles from the
-  // operands they read; otherwise by workgroups on the compute units its
-  // last wave of tiles leaves idle, when there are at least 16 of them and
-  // at most 128 rows each.
-  if (norms_in_layer1 && gemm_big_tiles(dt, g1)) {
-    g1.norm_tiles = 1;  // problem 0: layer 1 of f_V, A = V
+  // with 256 x 256 tiles (asked for with the norms: tiles of 192 rows cannot
+  // form them), by f_V's tiles from the operands they read; otherwise by
+  // workgroups on the compute units its last wave of 128 x 128 tiles leaves
+  // idle, when there are at least 16 of them and at most 128 rows each.
+  g1.norm_tiles = norms_in_layer1 ? 1 : 0;  // problem 0: layer 1 of f_V, A = V
+  if (!gemm_big_tiles(dt, g1)) g1.norm_tiles = 0;
+  if (g1.norm_tiles) {
     g1.norms = norms;
     g1.ninv = ninv;
-  } else if (norms_in_layer1 && gemm_direct_loads(dt, g1) && (reinterpret_cast<uintptr_t>(V) & 15) == 0) {
+  } else if (norms_in_layer1 && gemm_direct_loads(dt, g1) && !gemm_small_tiles(dt, g1) &&
+             (reinterpret_cast<uintptr_t>(V) & 15) == 0) {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) {
@@ -829,7 +831,8 @@ hipError_t enqueue_decoder(const map_decoder_weights& w, int B, const void* X, c
   g2.p[0] = linear(t.h, R, w.w_gate_up, nullptr, t.act, w.ff, w.d, EPI_SILU);
   g2.count = 1;
   // SiLU(gate) * up in the product's epilogue, on its float32 sums (2944 rows,
-  // 2 x 11008 columns: 130 MB not written and not read again, @@SILU@@);
+  // 2 x 11008 columns: 130 MB not written and not read again, a launch of 32
+  // us less and the product no slower);
   // weights that start off a 16-byte boundary run the register-staged
   // kernel, which leaves both halves to silu_mul
   const bool fused = gemm_direct_loads(MAP_BF16, g2);

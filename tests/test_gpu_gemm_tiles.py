@@ -93,3 +93,26 @@ def test_small_bf16_tiles_cosine(B, N, D):
     for b in range(B):
         assert float((S[b].double() - v[b] @ v[b].t()).abs().max()) < 1e-5
         assert torch.equal(S[b], S[b].t())
+
+
+# Layer-1 launches around the sizes where 192-row tiles, which cannot form
+# the row norms, would be the shortest, and small ones whose norms come from
+# the preparation: the call runs and its norms (through the gains) are right
+@pytest.mark.parametrize("B,N,M", [(8, 1000, (30, 45)), (9, 900, (60, 70)), (10, 1050, (20, 30)), (2, 500, (9, 20)), (1, 600, (40, 40))])
+def test_layer1_norms_across_tile_choices(B, N, M):
+    from paper_2608_06411_amd import map_prune
+    dev = device()
+    announce(f"layer-1 tile choices B={B} N={N} M={M}")
+    cfg = get_config("sweep", B=B, N=N, M=M, K=40, K0=20, clusters=90, pred=PredictorShape(D=256, D_h=1024, d_p=64))
+    x = make_inputs(cfg)
+    d = dev_inputs(x, dev)
+    o = map_prune(d["w"], d["V"], d["pos_v"], d["T"], d["pos_t"], x["t_off"], cfg.K, cfg.K0, cfg.tau)
+    p = o["p"].cpu().numpy().astype(np.float64)
+    p_ref = oracle.predicted_attention_batch(x["V_f32"], x["T_f32"], x["t_off"], x["pos_v"], x["pos_t"], oracle_weights(x),
+                                             cfg.pred.rope_theta)
+    np.testing.assert_allclose(p, p_ref, rtol=2e-2, atol=0)
+    order, gain = o["order"].cpu().numpy(), o["gain"].cpu().numpy()
+    for b in range(B):
+        rep = oracle.replay_check(p[b], x["V_f32"][b], cfg.K, cfg.K0, cfg.tau, order[b], gain[b])
+        assert rep.ok, f"image {b}: {rep.failure}"
+        assert rep.max_gain_rel_err < 1e-5
