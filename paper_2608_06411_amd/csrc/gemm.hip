@@ -497,7 +497,7 @@ __device__ __forceinline__ void store_rows(const GemmProblem& P, int bt, int m0,
   float bv[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) bv[k] = biased && k < n ? bf16_to_f32(bias[col + k]) : 0.0f;
-#pragma unroll 2
+#pragma unroll 4
   for (int r = tid / (W / 8); r < ROWS; r += NTH / (W / 8)) {
     const int row = m0 + r;
     if (row >= M) break;
@@ -640,7 +640,7 @@ __device__ __forceinline__ void cosine_store(const GemmProblem& P, int bt, int t
 // chunk the XOR swizzle puts there.  The stages are separate LDS arrays
 // addressed with compile-time stage numbers, so the only waits on those
 // loads are the explicit counted ones before each barrier.
-// Requirements (checked by the host): K % 256 == 0, lda and ldb multiples of
+// Requirements (checked by the host): K % 64 == 0, K >= 256, lda and ldb multiples of
 // 8, A and B 16-byte aligned, a staged epilogue (bias, cosine, direct) or
 // EPI_PARTIAL.
 
@@ -1085,7 +1085,7 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
   const int n0 = tn * (silu ? kBig / 2 : kBig);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
-  const int nk = P.K / 64;  // a multiple of 4 (checked by the host)
+  const int nk = P.K / 64;  // even (checked by the host)
   float rs_mine = 0.0f;     // cosine epilogue: 1/norm of tile row tid, or of column tid - 256
   if (P.epi == EPI_COSINE) {
     const int k = tid < kBig ? m0 + tid : n0 + tid - kBig;
@@ -1690,7 +1690,9 @@ bool gemm_direct_loads(map_dtype dt, const GemmBatch& g) {
   bool dma = true;  // every problem meets the direct-load requirements
   for (int i = 0; i < g.count; ++i) {
     const GemmProblem& p = g.p[i];
-    dma = dma && dma_epilogue(p.epi) && p.K % 256 == 0 && p.lda % 8 == 0 && p.ldb % 8 == 0 &&
+    // (128 x 128 tiles: whole slices, four at least; K % 256 sent widths such
+    // as 1152 to the register-staged kernel: 1450 x 2 tokens 59 us)
+    dma = dma && dma_epilogue(p.epi) && p.K % 64 == 0 && p.K >= 256 && p.lda % 8 == 0 && p.ldb % 8 == 0 &&
           (reinterpret_cast<uintptr_t>(p.A) & 15) == 0 && (reinterpret_cast<uintptr_t>(p.B) & 15) == 0 &&
           p.strideA % 8 == 0 && p.strideB % 8 == 0 &&
           k_ranges_ok(p);
@@ -1734,8 +1736,8 @@ static long long makespan(long long full, long long c, long long low, long long 
 // earliest; the others' tiles count as they are.
 static long long plan_big(const GemmBatch& g, GemmBatch& q, int& tm) {
   if (g.norm_blocks) return -1;
-  for (int i = 0; i < g.count; ++i)  // its loads' 32-bit byte offsets (an index map reaches kSubsetMaxN rows)
-    if (g.p[i].lda > (1 << 17) || g.p[i].ldb > (1 << 17) ||
+  for (int i = 0; i < g.count; ++i)  // slices in pairs; its loads' 32-bit byte offsets (an index map reaches kSubsetMaxN rows)
+    if (g.p[i].K % 128 != 0 || g.p[i].lda > (1 << 17) || g.p[i].ldb > (1 << 17) ||
         (g.p[i].epi == EPI_SILU && 2LL * g.p[i].ldb * (g.p[i].N + kBig) > INT32_MAX))
       return -1;
   if (g.norm_tiles > 0 && (g.norm_tiles > g.count || g.p[g.norm_tiles - 1].batch != 1)) return -1;

@@ -116,3 +116,22 @@ def test_layer1_norms_across_tile_choices(B, N, M):
         rep = oracle.replay_check(p[b], x["V_f32"][b], cfg.K, cfg.K0, cfg.tau, order[b], gain[b])
         assert rep.ok, f"image {b}: {rep.failure}"
         assert rep.max_gain_rel_err < 1e-5
+
+
+# K in whole slices of 64 but no multiple of 256: an odd count of slices, and
+# even ones on 128 x 128 and 256 x 256 tiles; five slices, and K below four
+# slices (the register-staged kernel)
+@pytest.mark.parametrize("B,N,D", [(1, 1500, 1088), (2, 1500, 1152), (16, 1000, 1152), (3, 700, 320), (2, 1500, 192)])
+def test_cosine_slice_counts(B, N, D):
+    from paper_2608_06411_amd import map_similarity
+    dev = device()
+    announce(f"slice counts, cosine B={B} N={N} D={D}")
+    g = torch.Generator(device=dev)
+    g.manual_seed(N + D)
+    V = torch.randn(B, N, D, generator=g, device=dev).to(torch.bfloat16)
+    S, norms = map_similarity(V)
+    for b in range(B):
+        v = V[b].double()
+        v = v / v.norm(dim=1, keepdim=True)
+        assert float((S[b].double() - v @ v.t()).abs().max()) < 1e-5
+        assert torch.equal(S[b], S[b].t())
