@@ -1178,6 +1178,7 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
     for (int b = 0; b < 2; ++b) {
       if (!sq[i][b]) continue;
       const uint4 u = half[at][64 * wm + 32 * b + lr][(2 * wn + lh) ^ swz(lr)];
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read before this phase's barrier: see slice()
       const uint32_t wv[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -1197,10 +1198,13 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
   };
   // One slice kt in buffer buf (= kt % 2, a constant in the unrolled body).
   // Hazards: a half-tile is reloaded one phase or more after the phase that
-  // read it, whose reads both groups have waited for by then (B0 is reloaded
-  // in the very next phase, so its reads are waited for before the first
-  // phase's barrier); the loads of slice kt + 1 are waited for in the last
-  // phase, before the barrier that lets either group read it.
+  // read it, whose reads both groups have waited for by then.  Reads of an
+  // array that is reloaded in the very next phase are waited for before their
+  // own phase's first barrier, since the other group may start that phase
+  // after it: B0's, and those that the row norms add (squares: the upper half
+  // of A in the second phase, the lower half in the last).  The loads of
+  // slice kt + 1 are waited for in the last phase, before the barrier that
+  // lets either group read it.
   auto slice = [&](int kt, int buf) {
     const bool more1 = kt + 1 < nk, more2 = kt + 2 < nk;
     read_b(4 * buf + 2, b0);
