@@ -1676,10 +1676,13 @@ static void finalize_tiles(GemmBatch& g, int tile) {
 void gemm_finalize(GemmBatch& g) { finalize_tiles(g, BM); }
 
 // K ranges of a split problem: equal ranges (K / ksplit) or kchunk-long ones
-// with a shorter last range, each a positive multiple of 256.
+// with a shorter last range, each a multiple of 256 but the last, which is
+// what K leaves: 256 at least, since the direct-load kernel starts with the
+// loads of four slices of 64 whatever the range's length (K itself is a
+// multiple of 64).
 static bool k_ranges_ok(const GemmProblem& p) {
   if (p.ksplit <= 1) return true;
-  if (p.kchunk > 0) return p.kchunk % 256 == 0 && (long long)(p.ksplit - 1) * p.kchunk < p.K;
+  if (p.kchunk > 0) return p.kchunk % 256 == 0 && p.K - (long long)(p.ksplit - 1) * p.kchunk >= 256;
   return p.K % p.ksplit == 0 && (p.K / p.ksplit) % 256 == 0;
 }
 

@@ -104,7 +104,8 @@ struct GemmProblem {
   const int32_t* mapB;
   long long mapStride;
   int ksplit;              // EPI_PARTIAL: K ranges per tile (K / ksplit each, a multiple of 256)
-  int kchunk;              // EPI_PARTIAL, if > 0: ranges of kchunk (a multiple of 256), the last shorter
+  int kchunk;              // EPI_PARTIAL, if > 0: ranges of kchunk (a multiple of 256), the last
+                           // what K leaves (256 at least)
   const int32_t* run_if;   // [batch] batch items whose flag is 0 are skipped (null: none)
   void* aux;               // EPI_GELU2: second output; EPI_MUL, EPI_RESID: the factor or the residual
                            // (each [M][ldc] of type T)
