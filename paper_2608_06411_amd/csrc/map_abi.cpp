@@ -773,16 +773,18 @@ DecoderWs carve_decoder(Carver& c, int R, const map_decoder_weights& w, int cus)
 
 // y = acc + residual: split over K into float32 partials and their ordered
 // sum (when the tiles alone would leave the device mostly idle), else the
-// residual epilogue.
+// residual epilogue.  K ranges exist in the direct-load kernel only: a product
+// that it does not take (weights that start off a 16-byte boundary) stays
+// whole, on the register-staged kernel.
 hipError_t resid_product(const void* A, int M, const void* W, int N, int K, const void* res, void* out, float* part,
                          int cus, const char* name, hipStream_t st) {
   GemmBatch g;
   memset(&g, 0, sizeof(g));
   g.p[0] = linear(A, M, W, nullptr, out, N, K, EPI_RESID);
   g.p[0].aux = const_cast<void*>(res);
-  split_k(g.p[0], cus);
-  if (g.p[0].epi == EPI_PARTIAL) g.p[0].C = part;
   g.count = 1;
+  if (gemm_direct_loads(MAP_BF16, g)) split_k(g.p[0], cus);
+  if (g.p[0].epi == EPI_PARTIAL) g.p[0].C = part;
   gemm_finalize(g);
   hipError_t e = launch_gemm(MAP_BF16, g, name, st);
   if (e != hipSuccess || g.p[0].epi != EPI_PARTIAL) return e;

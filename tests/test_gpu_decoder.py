@@ -178,3 +178,25 @@ def test_decoder_weights_off_alignment():
     got = mp.map_decoder_layer(mp.DecoderWeights(**wt, n_heads=H), x, pos, seq_off)
     du, dw = (got - x).double(), (want - x).double()
     assert float((du - dw).norm() / dw.norm()) <= 1e-2  # two bf16 roundings more (2^-9 each) in one path
+
+
+@pytest.mark.parametrize("name", ["w_qkv", "w_o", "w_gate_up", "w_down"])
+@pytest.mark.parametrize("rows", [[70, 63], [4400]])  # the products by w_o and w_down split over K; whole
+def test_decoder_each_weight_off_alignment(name, rows):
+    """Any one of the weights two bytes off a 16-byte boundary."""
+    import paper_2608_06411_amd as mp
+    dev = device()
+    d, H, ff = 512, 4, 768
+    announce(f"decoder, {name} off alignment, {sum(rows)} rows")
+    rng = np.random.default_rng(15)
+    seq_off = [0] + [int(v) for v in np.cumsum(rows)]
+    x = _dev(f32_to_bf16_bits(rng.standard_normal((seq_off[-1], d)).astype(np.float32)), dev)
+    pos = torch.arange(seq_off[-1], dtype=torch.int32, device=dev)
+    wt = {k: _dev(v, dev) for k, v in _weights(d, ff, 16, std=0.05).items()}
+    want = mp.map_decoder_layer(mp.DecoderWeights(**wt, n_heads=H), x, pos, seq_off)
+    flat = torch.empty(wt[name].numel() + 1, dtype=torch.bfloat16, device=dev)
+    flat[1:] = wt[name].reshape(-1)
+    wt[name] = flat[1:].view(wt[name].shape)
+    got = mp.map_decoder_layer(mp.DecoderWeights(**wt, n_heads=H), x, pos, seq_off)
+    du, dw = (got - x).double(), (want - x).double()
+    assert float((du - dw).norm() / dw.norm()) <= 1e-2  # the other kernel's sums may round a bf16 intermediate (2^-9) the other way
