@@ -1253,7 +1253,9 @@ static map_status prune_impl(const map_weights* w, map_dtype dt, int B, int N, c
   float* norms = c.take<float>((size_t)B * N);
   float* ninv = c.take<float>((size_t)B * N);
   float* p = p_out ? p_out : c.take<float>((size_t)B * N);
-  const int nc = subset_size(dt, N, w->D, sp);
+  // the subset's rows come through an index map, which the direct-load kernel
+  // alone follows: tokens off a 16-byte boundary take the full path
+  const int nc = (reinterpret_cast<uintptr_t>(V) & 15) == 0 ? subset_size(dt, N, w->D, sp) : 0;
   Layer0 l0{T, pos_t, t_off_host};
   const Layer0* l0p = layer0 ? &l0 : nullptr;
   if (nc > 0) {
