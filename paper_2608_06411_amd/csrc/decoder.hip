@@ -200,7 +200,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attention_kernel(const DecoderArgs
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[d4][r] = 0.0f;
   const float c2 = 1.4426950408889634f / sqrtf(static_cast<float>(DH));  // log2(e) / sqrt(d_h)
-  float m = -INFINITY, l = 0.0f;  // the row's factor 2^-m (both halves agree) and this half's sum
+  // The row's factor 2^-m (both halves agree) and this half's sum.  m starts
+  // below every finite score but finite, so that a row whose scores so far
+  // are all -inf (products past float32's range) has zero probabilities there
+  // and not 2^(-inf + inf).
+  float m = -3.0e38f, l = 0.0f;
 
   load_k(0);
   load_v(0);
@@ -242,7 +246,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attention_kernel(const DecoderArgs
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[t][r]);
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
     if (__any(mx > m + kRescale)) {
-      const float mn = fmaxf(m, mx), al = __builtin_amdgcn_exp2f(m - mn);  // (first block: 2^-inf = 0)
+      const float mn = fmaxf(m, mx), al = __builtin_amdgcn_exp2f(m - mn);  // (first finite block: 0)
       m = mn;
       l *= al;
 #pragma unroll

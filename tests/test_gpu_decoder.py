@@ -200,3 +200,28 @@ def test_decoder_each_weight_off_alignment(name, rows):
     got = mp.map_decoder_layer(mp.DecoderWeights(**wt, n_heads=H), x, pos, seq_off)
     du, dw = (got - x).double(), (want - x).double()
     assert float((du - dw).norm() / dw.norm()) <= 1e-2  # the other kernel's sums may round a bf16 intermediate (2^-9) the other way
+
+
+@pytest.mark.parametrize("lens", [[200], [129] * 60 + [600]])  # 64 and 128 query rows per workgroup
+def test_decoder_attention_scores_past_float32(lens):
+    """Keys whose scores are below float32's range (-1e50: -inf in the products)
+    fill a sequence's first key block for the rows after it: they weigh
+    nothing, and the rows' update meets the update's bar."""
+    d, H, ff = 256, 2, 256
+    announce(f"decoder attention, scores past float32, {len(lens)} sequences")
+    rng = np.random.default_rng(17)
+    seq_off = [0] + [int(v) for v in np.cumsum(lens)]
+    place = np.concatenate([np.arange(n) for n in lens])
+    x = rng.standard_normal((seq_off[-1], d)).astype(np.float32)
+    x[:, 0] = np.where(place < 64, 2.0, 0.0)   # the far keys ...
+    x[:, 1] = np.where(place < 64, 0.0, 2.0)   # ... and the queries that see them so
+    X = f32_to_bf16_bits(x)
+    wb = _weights(d, ff, 18, std=0.05)
+    w = bf16_bits_to_f32(wb["w_qkv"])
+    w[63] = w[d + 63] = 0.0                     # head 0's slowest pair: angles of at most 0.05
+    w[127] = w[d + 127] = 0.0
+    w[63, 1], w[d + 63, 0] = 1e25, -1e25
+    wb["w_qkv"] = f32_to_bf16_bits(w)
+    pos = (place % 400).astype(np.int32)
+    got = _run_and_check(X, pos, seq_off, wb, H, "scores past float32")
+    assert np.isfinite(got).all()
