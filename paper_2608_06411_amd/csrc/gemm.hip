@@ -175,19 +175,25 @@ __device__ __forceinline__ void decode_tile(const GemmBatch& args, int& pi, int&
 // Epilogues on a tile of 64 IB x 64 JB, four waves (wm, wn) of 32 IB x 32 JB.
 // The RoPE epilogue (128 x 128 tiles only) stages the tile through LDS: rows
 // 0..63 in tile_lo, rows 64..127 in tile_hi (64 x 128 floats each).
+// 128 x 128 tiles form row and column where they use them: with the wave's
+// first row and column formed ahead, as 64 x 64 tiles have it, the compiler's
+// register allocation makes the register-staged kernel's tiles slower (3 x 1225
+// rows of 1160 with GELU 36 -> 40 us, 2880 of 4104 78 -> 84).
 template <typename T, int IB, int JB>
 __device__ __forceinline__ void epilogue(const GemmProblem& P, int bt, int tm, int tn, f32x16_t (&acc)[IB][JB],
                                          float* tile_lo, float* tile_hi, int tid, int lane, int wm, int wn) {
   const int M = P.M, N = P.N;
   const int m0 = tm * 64 * IB, n0 = tn * 64 * JB;
   const int wr = m0 + wm * 32 * IB, wc = n0 + wn * 32 * JB;  // this wave's first row and column
+  auto row_at = [&](int i) { return IB == 1 ? wr : m0 + wm * (32 * IB) + i * 32; };
+  auto col_at = [&](int j) { return JB == 1 ? wc : n0 + wn * (32 * JB) + j * 32; };
   if (epi_direct(P.epi)) {
     const int e = P.epi;
     const T* __restrict__ bias = static_cast<const T*>(P.bias);
     const long long base = bt * P.strideC;
 #pragma unroll
     for (int j = 0; j < JB; ++j) {
-      const int col = wc + j * 32 + acc_col(lane);
+      const int col = col_at(j) + acc_col(lane);
       if (col >= N) continue;
       const float bv = (e == EPI_GELU2 && bias) ? to_f32<T>(bias[col]) : 0.0f;
 #pragma unroll
@@ -199,13 +205,13 @@ __device__ __forceinline__ void epilogue(const GemmProblem& P, int bt, int tm, i
           const T* __restrict__ aux = static_cast<const T*>(P.aux) + base;
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int row = min(wr + i * 32 + acc_row(r, lane), M - 1);
+            const int row = min(row_at(i) + acc_row(r, lane), M - 1);
             f[r] = to_f32<T>(aux[(long long)row * P.ldc + col]);
           }
         }
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = wr + i * 32 + acc_row(r, lane);
+          const int row = row_at(i) + acc_row(r, lane);
           if (row >= M) continue;
           const long long at = base + (long long)row * P.ldc + col;
           const float v = acc[i][j][r] + bv;
@@ -228,14 +234,14 @@ __device__ __forceinline__ void epilogue(const GemmProblem& P, int bt, int tm, i
     const bool gelu = P.epi == EPI_BIAS_GELU;
 #pragma unroll
     for (int j = 0; j < JB; ++j) {
-      const int col = wc + j * 32 + acc_col(lane);
+      const int col = col_at(j) + acc_col(lane);
       if (col >= N) continue;
       const float bv = bias ? to_f32<T>(bias[col]) : 0.0f;
 #pragma unroll
       for (int i = 0; i < IB; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = wr + i * 32 + acc_row(r, lane);
+          const int row = row_at(i) + acc_row(r, lane);
           if (row >= M) continue;
           float v = acc[i][j][r] + bv;
           if (gelu) v = gelu_erf(v);
@@ -252,14 +258,14 @@ __device__ __forceinline__ void epilogue(const GemmProblem& P, int bt, int tm, i
     const bool vec4 = (P.ldc & 3) == 0;
 #pragma unroll
     for (int j = 0; j < JB; ++j) {
-      const int col = wc + j * 32 + acc_col(lane);
+      const int col = col_at(j) + acc_col(lane);
       if (col >= N) continue;
       const float sc = rs[col];
 #pragma unroll
       for (int i = 0; i < IB; ++i)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int row0 = wr + i * 32 + 8 * q + 4 * (lane >> 5);
+          const int row0 = row_at(i) + 8 * q + 4 * (lane >> 5);
           float v[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
