@@ -143,6 +143,19 @@ __device__ __forceinline__ void mma_slice<float>(const uint4 (*As)[8], const uin
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 __device__ __forceinline__ int acc_col(int lane) { return lane & 31; }
 
+// The problem that holds `tile`, and the tile's number in it.
+__device__ __forceinline__ int find_problem(const GemmBatch& args, int tile, int& local) {
+  int pi = 0, begin = 0;
+#pragma unroll
+  for (int q = 1; q < kMaxGemmProblems; ++q)
+    if (q < args.count && tile >= args.begin[q]) {
+      pi = q;
+      begin = args.begin[q];
+    }
+  local = tile - begin;
+  return pi;
+}
+
 // Workgroup -> (problem, batch item, tile row, tile column).
 // The tiles before args.first_tiles run first, each class XCD-contiguous:
 // the launch puts the short tiles into the second class.
@@ -152,12 +165,8 @@ __device__ __forceinline__ void decode_tile(const GemmBatch& args, int& pi, int&
                                             int& local) {
   const int b = blockIdx.x, f = args.first_tiles;
   const int tile = b < f ? xcd_remap(b, f) : f + xcd_remap(b - f, args.total_tiles - f);
-  pi = 0;
-#pragma unroll
-  for (int q = 1; q < kMaxGemmProblems; ++q)
-    if (q < args.count && tile >= args.p[q].tile_begin) pi = q;
+  pi = find_problem(args, tile, local);
   const GemmProblem& P = args.p[pi];
-  local = tile - P.tile_begin;
   bt = local / P.tiles_per_batch;
   int tt = local - bt * P.tiles_per_batch;
   kc = tt / P.tiles_tri;
@@ -1067,12 +1076,9 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
   __shared__ float rs_big[2 * kBig];  // cosine: 1/norm of the tile's rows, then columns
   const int f = args.first_tiles, blk = blockIdx.x;
   const int tile = blk < f ? xcd_remap(blk, f) : f + xcd_remap(blk - f, args.total_tiles - f);
-  int pi = 0;
-#pragma unroll
-  for (int q = 1; q < kMaxGemmProblems; ++q)
-    if (q < args.count && tile >= args.p[q].tile_begin) pi = q;
+  int local;
+  const int pi = find_problem(args, tile, local);
   const GemmProblem& P = args.p[pi];
-  const int local = tile - P.tile_begin;
   const int bt = local / P.tiles_per_batch;
   int tt = local - bt * P.tiles_per_batch, tm, tn;
   if (P.triangular) {  // upper triangle, row by row: row tm holds tiles_n - tm tiles
@@ -1659,7 +1665,7 @@ static void count_tiles(GemmBatch& g, int wide) {
     p.tiles_n = col_tiles(p, wide);
     p.tiles_tri = p.triangular ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
     p.tiles_per_batch = p.tiles_tri * (p.ksplit > 1 ? p.ksplit : 1);
-    p.tile_begin = begin;
+    g.begin[i] = begin;
     begin += p.tiles_per_batch * p.batch;
   }
   g.total_tiles = begin;
@@ -1676,7 +1682,7 @@ static void finalize_tiles(GemmBatch& g, int tile) {
   // (three 1225-token images: 69 us, now 52).
   int q = g.count;
   while (q > 1 && 2 * g.p[q - 1].K <= g.p[0].K) --q;
-  g.first_tiles = q < g.count ? g.p[q].tile_begin : 0;
+  g.first_tiles = q < g.count ? g.begin[q] : 0;
 }
 
 void gemm_finalize(GemmBatch& g) { finalize_tiles(g, BM); }
@@ -1829,7 +1835,7 @@ static long long plan_big(const GemmBatch& g, GemmBatch& q, int& tm) {
   }
   const int first = q.first_tiles;
   count_tiles(q, kBig);
-  q.first_tiles = first > 0 && first < q.count ? q.p[first].tile_begin : 0;
+  q.first_tiles = first > 0 && first < q.count ? q.begin[first] : 0;
   return best;
 }
 

@@ -110,16 +110,21 @@ struct GemmProblem {
   void* aux;               // EPI_GELU2: second output; EPI_MUL, EPI_RESID: the factor or the residual
                            // (each [M][ldc] of type T)
   // filled by the host helper
-  int tiles_m, tiles_n, tiles_tri, tiles_per_batch, tile_begin;
+  int tiles_m, tiles_n, tiles_tri, tiles_per_batch;
   int th;       // rows of a tile
   int norm_at;  // 256-column tiles: 1 + the row of norms that row 0 of A has (0: no norms)
 };
 
 constexpr int kMaxGemmProblems = 7;  // (a launch brings at most six; one may be cut in two)
 struct GemmBatch {
-  GemmProblem p[kMaxGemmProblems];
+  // What every workgroup reads to find its problem comes first, in one cache
+  // line: these are kernel arguments, and each line of them is a trip to
+  // memory at a workgroup's start (with the first tiles in the problems
+  // themselves, seven lines: 2 x 1450 tokens of 1160 41.3 us, now 41.0; the
+  // subset's product of one image 11.6, now 11.45).
   int count;
   int total_tiles;
+  int begin[kMaxGemmProblems];  // each problem's first tile
   int first_tiles;  // tiles dispatched before the rest (0: one class)
   // bf16 direct-load launches only: norm_blocks more workgroups, dispatched
   // after every tile (on compute units the tiles leave idle), write the row
@@ -134,6 +139,7 @@ struct GemmBatch {
   // tiles of problem q (batch 1) also write the row norms of its A rows and
   // their reciprocals (norm_blocks must be 0), each row by one tile column
   int norm_tiles;
+  GemmProblem p[kMaxGemmProblems];
 };
 
 void gemm_finalize(GemmBatch& g);  // computes the tile counts
