@@ -459,6 +459,28 @@ __device__ __forceinline__ void stage_acc(const f32x16_t (&acc)[2][J], const Sta
         L.row(wm * (32 * IB) + i * 32 + acc_row(r, lane))[wn * (32 * J) + j * 32 + acc_col(lane)] = acc[i][j][r];
 }
 
+// The 128 x 128 kernel's tile with the bias, and GELU when asked, applied in
+// registers on the way in: its eight waves hold 64 x 32 entries each, so this
+// runs without the addresses and tests of the way out.  (In the loop on the way
+// out one image's layer 1 took 42.2 us against 40.7 so, three of 1225 tokens
+// 52.0 against 50.5.  The 256 x 256 kernel keeps it there: its two passes per
+// half-tile need the smaller code.)
+__device__ __forceinline__ void stage_bias(const GemmProblem& P, int n0, const f32x16_t (&acc)[2][1], const StagedTile& L,
+                                           int lane, int wm, int wn) {
+  const bf16_t* __restrict__ bias = static_cast<const bf16_t*>(P.bias);
+  const bool gelu = P.epi == EPI_BIAS_GELU;
+  const int cl = wn * 32 + acc_col(lane);
+  const float bv = bias && n0 + cl < P.N ? bf16_to_f32(bias[n0 + cl]) : 0.0f;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float v = acc[i][0][r] + bv;
+      if (gelu) v = gelu_erf(v);
+      L.row(wm * 64 + i * 32 + acc_row(r, lane))[cl] = v;
+    }
+}
+
 __device__ __forceinline__ uint4 pack_bf16x8(const float (&f)[8]) {
   uint4 o;
   o.x = f32_to_bf16(f[0]) | (static_cast<uint32_t>(f32_to_bf16(f[1])) << 16);
@@ -494,11 +516,13 @@ __device__ __forceinline__ void store_bf16x8(bf16_t* dst, bool vec, int n, const
 // The row-wise epilogues over a staged tile of ROWS rows by W = 128 or 256
 // columns (columns 0..127 in L0, 128.. in L1): bias (+ GELU), float32,
 // GELU and GELU' of acc + bias, acc times or plus the bf16 aux entry; every
-// global access moves 16 bytes along a row.
-template <int W, int NTH, int ROWS = BM>
+// global access moves 16 bytes along a row.  E: the epilogue where the caller
+// knows it (kEpiAny: P.epi; kEpiFinal: the entries are final, only rounded).
+constexpr int kEpiAny = -1, kEpiFinal = -2;
+template <int W, int NTH, int ROWS = BM, int E = kEpiAny>
 __device__ __forceinline__ void store_rows(const GemmProblem& P, int bt, int m0, int n0, const StagedTile& L0,
                                            const StagedTile& L1, int tid) {
-  const int M = P.M, N = P.N, e = P.epi;
+  const int M = P.M, N = P.N, e = E == kEpiAny ? P.epi : E;
   const bf16_t* __restrict__ bias = static_cast<const bf16_t*>(P.bias);
   const long long base = bt * P.strideC;
   const bool aligned = (P.ldc & 7) == 0 && (reinterpret_cast<uintptr_t>(P.C) & 15) == 0 &&
@@ -770,6 +794,9 @@ __device__ __forceinline__ void norm_rows(const GemmBatch& args, int blk) {
 
 constexpr int kDmaThreads = 512;
 
+// SILU: every problem is EPI_SILU, 64 gate columns, then the same columns of up
+// (rows N.. of B); else none is.
+template <bool SILU>
 __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch args) {
   __shared__ uint4 st0[2][BM][8], st1[2][BM][8], st2[2][BM][8], st3[2][BM][8], st4[2][BM][8];  // 5 x 32 KiB
   if (static_cast<int>(blockIdx.x) >= args.total_tiles) {
@@ -786,8 +813,7 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
   const int kl = P.ksplit > 1 ? (P.kchunk > 0 ? P.kchunk : P.K / P.ksplit) : P.K;
   const bf16_t* __restrict__ A = static_cast<const bf16_t*>(P.A) + bt * P.strideA + (long long)kc * kl;
   const bf16_t* __restrict__ B = static_cast<const bf16_t*>(P.B) + bt * P.strideB + (long long)kc * kl;
-  const bool silu = P.epi == EPI_SILU;  // 64 gate columns, then the same columns of up (rows N.. of B)
-  const int m0 = tm * BM, n0 = tn * (silu ? BN / 2 : BN);
+  const int m0 = tm * BM, n0 = tn * (SILU ? BN / 2 : BN);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 2, wn = wave & 3;
   const int nk = min(kl, P.K - kc * kl) / 64;
@@ -809,7 +835,7 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
   for (int j = 0; j < 2; ++j) {
     const int r = 16 * wave + 8 * j + (lane >> 3);
     const int v = (lane & 7) ^ swz(r);  // the chunk the swizzle puts at position lane & 7 of row r
-    const int ra = min(m0 + r, M - 1), rb = silu ? (r < 64 ? min(n0 + r, N - 1) : N + min(n0 + r - 64, N - 1)) : min(n0 + r, N - 1);
+    const int ra = min(m0 + r, M - 1), rb = SILU ? (r < 64 ? min(n0 + r, N - 1) : N + min(n0 + r - 64, N - 1)) : min(n0 + r, N - 1);
     ga[j] = A + (long long)(mapA ? mapA[ra] : ra) * P.lda + 8 * v;
     gb[j] = B + (long long)(mapB ? mapB[rb] : rb) * P.ldb + 8 * v;
   }
@@ -882,15 +908,26 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
   }
   const StagedTile L{reinterpret_cast<float*>(&st0[0][0][0]), reinterpret_cast<float*>(&st1[0][0][0]),
                      reinterpret_cast<float*>(&st2[0][0][0]), reinterpret_cast<float*>(&st3[0][0][0])};
+  if constexpr (SILU) {
+    stage_acc<1>(acc, L, lane, wm, wn);
+    __syncthreads();
+    store_silu<BN / 2, kDmaThreads>(P, bt, m0, n0, L, L, tid);
+    return;
+  }
+  const bool biased = P.epi == EPI_BIAS_GELU || P.epi == EPI_BIAS;
   if (P.epi == EPI_COSINE)
     cosine_stage<1>(acc, L, rs_tile, rs_tile + BM, lane, wm, wn);
+  else if (biased)
+    stage_bias(P, n0, acc, L, lane, wm, wn);
   else
     stage_acc<1>(acc, L, lane, wm, wn);
   __syncthreads();
   if (P.epi == EPI_COSINE)
     cosine_store<kDmaThreads>(P, bt, tm, tn, L, tid);
-  else if (silu)
-    store_silu<BN / 2, kDmaThreads>(P, bt, m0, n0, L, L, tid);
+  else if (biased)
+    store_rows<BN, kDmaThreads, BM, kEpiFinal>(P, bt, m0, n0, L, L, tid);
+  else if (P.epi == EPI_F32)
+    store_rows<BN, kDmaThreads, BM, EPI_F32>(P, bt, m0, n0, L, L, tid);
   else
     store_rows<BN, kDmaThreads>(P, bt, m0, n0, L, L, tid);
 }
@@ -1704,9 +1741,16 @@ static bool dma_epilogue(int e) {
   return e == EPI_BIAS_GELU || e == EPI_BIAS || e == EPI_COSINE || e == EPI_PARTIAL || e == EPI_SILU || epi_direct(e);
 }
 
+static int silu_problems(const GemmBatch& g) {
+  int n = 0;
+  for (int i = 0; i < g.count; ++i) n += g.p[i].epi == EPI_SILU;
+  return n;
+}
+
 bool gemm_direct_loads(map_dtype dt, const GemmBatch& g) {
   if (dt != MAP_BF16) return false;
-  bool dma = true;  // every problem meets the direct-load requirements
+  const int silu = silu_problems(g);  // all of a launch's problems or none
+  bool dma = silu == 0 || silu == g.count;  // every problem meets the direct-load requirements
   for (int i = 0; i < g.count; ++i) {
     const GemmProblem& p = g.p[i];
     // (128 x 128 tiles: whole slices, four at least; K % 256 sent widths such
@@ -1913,7 +1957,8 @@ hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipSt
       return launch_kernel(name, gemm_tile64_kernel<bf16_t>, dim3(q.total_tiles), dim3(kTileThreads), 0, s, q);
     }
     if (dma)
-      return launch_kernel(name, gemm_dma_kernel, dim3(g.total_tiles + g.norm_blocks), dim3(kDmaThreads), 0, s, g);
+      return launch_kernel(name, silu_problems(g) > 0 ? gemm_dma_kernel<true> : gemm_dma_kernel<false>,
+                           dim3(g.total_tiles + g.norm_blocks), dim3(kDmaThreads), 0, s, g);
     if (g.norm_blocks) return hipErrorInvalidValue;
     for (int i = 0; i < g.count; ++i)  // index maps and K ranges exist in the direct-load kernel only
       if (g.p[i].epi == EPI_PARTIAL || g.p[i].epi == EPI_SILU || g.p[i].mapA || g.p[i].mapB) return hipErrorInvalidValue;
