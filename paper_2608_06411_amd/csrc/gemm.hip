@@ -1836,15 +1836,19 @@ static long long plan_big(const GemmBatch& g, GemmBatch& q, int& tm) {
     }
     const int M = cut >= 0 ? g.p[cut].M : 0;
     const long long b = cut >= 0 ? col_tiles(g.p[cut], kBig) : 0;
-    for (int f = M / t + (M % t > 128); f >= 0; --f) {  // f tile rows of t, the rest of 128
-      const int rest = std::max(0, M - f * t);
+    // f tile rows of t, the rest of 128.  Of the f with one number of rounds
+    // of full tiles the largest is never the dearer: one row of them less
+    // leaves units free for at most the tiles of 128 that take its place.
+    for (long long f = M / t + (M % t > 128); f >= 0;) {
+      const int rest = static_cast<int>(std::max(0LL, M - f * t));
       const long long cost = makespan(full + f * b, c, low + (rest + 127) / 128 * b, cus);
       if (best < 0 || cost < best) {
         best = cost;
         best_tm = t;
-        best_rows = std::min(M, f * t);
+        best_rows = static_cast<int>(std::min<long long>(M, f * t));
       }
-      if (cut < 0) break;
+      const long long fewer = ((full + f * b + cus - 1) / cus - 1) * cus - full;  // full tiles in one round less
+      f = cut < 0 || fewer < 0 ? -1 : fewer / b;
     }
   }
   tm = best_tm;
@@ -1942,13 +1946,13 @@ bool gemm_small_tiles(map_dtype dt, const GemmBatch& g) {
 
 hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipStream_t s) {
   if (g.total_tiles == 0) return hipSuccess;
-  // the in-tile row norms exist in the 256 x 256 kernel only
-  if (g.norm_tiles > 0 && !gemm_big_tiles(dt, g)) return hipErrorInvalidValue;
   if (dt == MAP_BF16) {
     const bool dma = gemm_direct_loads(dt, g);
     GemmBatch q;
     int tm;
-    if (dma && big_tiles_pay(g, q, tm))
+    const bool big = dma && big_tiles_pay(g, q, tm);
+    if (g.norm_tiles > 0 && !big) return hipErrorInvalidValue;  // the in-tile row norms exist there only
+    if (big)
       return launch_kernel(name, g.norm_tiles ? gemm_big_kernel<true, 256> : tm == 192 ? gemm_big_kernel<false, 192> : gemm_big_kernel<false, 256>,
                            dim3(q.total_tiles), dim3(kBigThreads), 0, s, q);
     if (dma && tile64_fits(g, 8, 64) && tile64_pays(g)) {
@@ -1964,6 +1968,7 @@ hipError_t launch_gemm(map_dtype dt, const GemmBatch& g, const char* name, hipSt
       if (g.p[i].epi == EPI_PARTIAL || g.p[i].epi == EPI_SILU || g.p[i].mapA || g.p[i].mapB) return hipErrorInvalidValue;
     return launch_kernel(name, gemm_kernel<bf16_t>, dim3(g.total_tiles), dim3(NT), 0, s, g);
   }
+  if (g.norm_tiles > 0) return hipErrorInvalidValue;
   if (tile64_fits(g, 4, 32)) {
     GemmBatch q = g;
     finalize_tiles(q, kTile);
