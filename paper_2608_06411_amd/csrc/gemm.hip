@@ -442,21 +442,18 @@ struct StagedTile {
   __device__ float* col_chunk(int c, int ch) const { return (c < 64 ? t0 : t1) + (c & 63) * BM + 4 * (ch ^ (c & 31)); }
 };
 
-// The staged epilogues take the accumulators of either layout of a 128 x
-// 128 tile: J = 2, four waves (wm, wn) of 64 x 64 (2 x 2 blocks, columns
-// 64 wn + 32 j), 256 threads; J = 1, eight waves (wm, wn) of 64 x 32 (rows
-// 64 wm + 32 i, columns 32 wn), 512 threads.  They go to LDS as they are;
-// the element-wise part runs on the way out, in one compact loop.
+// The staged epilogues take a 128 x 128 tile from eight waves (wm, wn) of 64 x
+// 32 (rows 64 wm + 32 i, columns 32 wn), 512 threads.  Here the accumulators go
+// to LDS as they are; the element-wise part runs on the way out (store_rows,
+// store_silu).
 // IB = 1 (256 x 256 kernel only): the wave's first block alone, rows 32 wm.
-template <int J, int IB = 2>
-__device__ __forceinline__ void stage_acc(const f32x16_t (&acc)[2][J], const StagedTile& L, int lane, int wm, int wn) {
+template <int IB = 2>
+__device__ __forceinline__ void stage_acc(const f32x16_t (&acc)[2][1], const StagedTile& L, int lane, int wm, int wn) {
 #pragma unroll
-  for (int j = 0; j < J; ++j)
+  for (int i = 0; i < IB; ++i)
 #pragma unroll
-    for (int i = 0; i < IB; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        L.row(wm * (32 * IB) + i * 32 + acc_row(r, lane))[wn * (32 * J) + j * 32 + acc_col(lane)] = acc[i][j][r];
+    for (int r = 0; r < 16; ++r)
+      L.row(wm * (32 * IB) + i * 32 + acc_row(r, lane))[wn * 32 + acc_col(lane)] = acc[i][0][r];
 }
 
 // The 128 x 128 kernel's tile with the bias, and GELU when asked, applied in
@@ -601,27 +598,23 @@ __device__ __forceinline__ void store_silu(const GemmProblem& P, int bt, int m0,
 // (row, col) and (col, row) from the same float, so S is bitwise symmetric.
 // A diagonal tile takes the entries below its diagonal from the transposed
 // copy (the mirror of the entries above it).
-template <int J>
-__device__ __forceinline__ void cosine_stage(f32x16_t (&acc)[2][J], const StagedTile& L, const float* rs_rows,
+__device__ __forceinline__ void cosine_stage(f32x16_t (&acc)[2][1], const StagedTile& L, const float* rs_rows,
                                              const float* rs_cols, int lane, int wm, int wn) {
+  const int cl = wn * 32 + acc_col(lane);
+  const float sc = rs_cols[cl];
 #pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int cl = wn * (32 * J) + j * 32 + acc_col(lane);
-    const float sc = rs_cols[cl];
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int q = 0; q < 4; ++q) {
+      const int rl0 = wm * 64 + i * 32 + 8 * q + 4 * (lane >> 5);
+      float v[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int rl0 = wm * 64 + i * 32 + 8 * q + 4 * (lane >> 5);
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          v[e] = acc[i][j][4 * q + e] * (rs_rows[rl0 + e] * sc);
-          L.row(rl0 + e)[cl] = v[e];
-        }
-        *reinterpret_cast<float4*>(L.col_chunk(cl, rl0 >> 2)) = make_float4(v[0], v[1], v[2], v[3]);
+      for (int e = 0; e < 4; ++e) {
+        v[e] = acc[i][0][4 * q + e] * (rs_rows[rl0 + e] * sc);
+        L.row(rl0 + e)[cl] = v[e];
       }
-  }
+      *reinterpret_cast<float4*>(L.col_chunk(cl, rl0 >> 2)) = make_float4(v[0], v[1], v[2], v[3]);
+    }
 }
 
 template <int NTH>
@@ -909,18 +902,18 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
   const StagedTile L{reinterpret_cast<float*>(&st0[0][0][0]), reinterpret_cast<float*>(&st1[0][0][0]),
                      reinterpret_cast<float*>(&st2[0][0][0]), reinterpret_cast<float*>(&st3[0][0][0])};
   if constexpr (SILU) {
-    stage_acc<1>(acc, L, lane, wm, wn);
+    stage_acc(acc, L, lane, wm, wn);
     __syncthreads();
     store_silu<BN / 2, kDmaThreads>(P, bt, m0, n0, L, L, tid);
     return;
   }
   const bool biased = P.epi == EPI_BIAS_GELU || P.epi == EPI_BIAS;
   if (P.epi == EPI_COSINE)
-    cosine_stage<1>(acc, L, rs_tile, rs_tile + BM, lane, wm, wn);
+    cosine_stage(acc, L, rs_tile, rs_tile + BM, lane, wm, wn);
   else if (biased)
     stage_bias(P, n0, acc, L, lane, wm, wn);
   else
-    stage_acc<1>(acc, L, lane, wm, wn);
+    stage_acc(acc, L, lane, wm, wn);
   __syncthreads();
   if (P.epi == EPI_COSINE)
     cosine_store<kDmaThreads>(P, bt, tm, tn, L, tid);
@@ -1392,13 +1385,13 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
       __syncthreads();  // the staging is free (and rs_big written)
       const float *rr = rs_big + 128 * i, *rc = rs_big + kBig + 128 * j;
       if (q == 0)
-        cosine_stage<1>(acc[0][0], LC, rr, rc, lane, wm, wn);
+        cosine_stage(acc[0][0], LC, rr, rc, lane, wm, wn);
       else if (q == 1)
-        cosine_stage<1>(acc[0][1], LC, rr, rc, lane, wm, wn);
+        cosine_stage(acc[0][1], LC, rr, rc, lane, wm, wn);
       else if (q == 2)
-        cosine_stage<1>(acc[1][0], LC, rr, rc, lane, wm, wn);
+        cosine_stage(acc[1][0], LC, rr, rc, lane, wm, wn);
       else
-        cosine_stage<1>(acc[1][1], LC, rr, rc, lane, wm, wn);
+        cosine_stage(acc[1][1], LC, rr, rc, lane, wm, wn);
       __syncthreads();
       cosine_store<kBigThreads>(P, bt, tm1, tn1, LC, tid);
     }
@@ -1406,8 +1399,8 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
   }
   // 128 rows by 256 columns at a time (the lower half of TM = 192: 64)
   const StagedTile L0{stage0, stage0 + 64 * BN, nullptr, nullptr}, L1{stage1, stage1 + 64 * BN, nullptr, nullptr};
-  stage_acc<1>(acc[0][0], L0, lane, wm, wn);
-  stage_acc<1>(acc[0][1], L1, lane, wm, wn);
+  stage_acc(acc[0][0], L0, lane, wm, wn);
+  stage_acc(acc[0][1], L1, lane, wm, wn);
   __syncthreads();
   if (silu)
     store_silu<kBig / 2, kBigThreads>(P, bt, m0, n0, L0, L1, tid);
@@ -1415,8 +1408,8 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
     store_rows<kBig, kBigThreads>(P, bt, m0, n0, L0, L1, tid);
   if (low) return;
   __syncthreads();  // the staging is read out
-  stage_acc<1, kLow>(acc[1][0], L0, lane, wm, wn);
-  stage_acc<1, kLow>(acc[1][1], L1, lane, wm, wn);
+  stage_acc<kLow>(acc[1][0], L0, lane, wm, wn);
+  stage_acc<kLow>(acc[1][1], L1, lane, wm, wn);
   __syncthreads();
   if (silu)
     store_silu<kBig / 2, kBigThreads, 64 * kLow>(P, bt, m0 + 128, n0, L0, L1, tid);
