@@ -15,8 +15,29 @@ PROBE = r"""
 #include "internal.h"
 using namespace mapk;
 
-// K ksplit kchunk offset: one bf16 problem of 300 x 200 whose B starts `offset` bytes past a 16-byte boundary
+// K ksplit kchunk offset: one bf16 problem of 300 x 200 whose B starts `offset` bytes past a 16-byte boundary.
+// cosine B N D: which kernel takes the upper triangle of B cosine matrices.
 int main(int argc, char** argv) {
+  if (argc == 5 && !strcmp(argv[1], "cosine")) {
+    GemmBatch g;
+    memset(&g, 0, sizeof(g));
+    GemmProblem& p = g.p[0];
+    p.batch = atoi(argv[2]);
+    p.M = p.N = p.ldc = atoi(argv[3]);
+    p.K = p.lda = p.ldb = atoi(argv[4]);
+    p.strideA = p.strideB = (long long)p.N * p.K;
+    p.epi = EPI_COSINE;
+    p.triangular = 1;
+    p.A = p.B = reinterpret_cast<const void*>(0x10000);
+    g.count = 1;
+    gemm_finalize(g);
+    const char* name = "staged";
+    if (gemm_big_tiles(MAP_BF16, g)) name = "big";
+    else if (gemm_small_tiles(MAP_BF16, g)) name = "small";
+    else if (gemm_direct_loads(MAP_BF16, g)) name = "128";
+    printf("%s\n", name);
+    return 0;
+  }
   for (int i = 1; i + 3 < argc; i += 4) {
     GemmBatch g;
     memset(&g, 0, sizeof(g));
@@ -41,7 +62,7 @@ int main(int argc, char** argv) {
 
 
 @pytest.fixture(scope="module")
-def direct_loads(tmp_path_factory):
+def probe(tmp_path_factory):
     if not os.path.exists(B.LIB):
         pytest.fail("libmap.so is not built (run python -m paper_2608_06411_amd.build)")
     d = tmp_path_factory.mktemp("probe")
@@ -50,12 +71,24 @@ def direct_loads(tmp_path_factory):
         f.write(PROBE)
     subprocess.run([B.hipcc(), "-std=c++17", "-I", B.INCLUDE, "-I", B.CSRC, "-x", "hip", "--offload-host-only", src,
                     "-x", "none", B.LIB, f"-Wl,-rpath,{os.path.dirname(B.LIB)}", "-o", exe], check=True, capture_output=True)
+    return lambda *args: subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True).stdout.split()
 
-    def ask(*problems):
-        out = subprocess.run([exe, *[str(v) for p in problems for v in p]], check=True, capture_output=True, text=True)
-        return [v == "1" for v in out.stdout.split()]
 
-    return ask
+@pytest.fixture(scope="module")
+def direct_loads(probe):
+    return lambda *problems: [v == "1" for v in probe(*[v for p in problems for v in p])]
+
+
+@pytest.mark.parametrize("B,N,D,kernel", [
+    (16, 1000, 256, "big"), (20, 769, 512, "big"), (16, 1000, 1152, "big"),
+    (1, 65, 256, "small"), (3, 33, 512, "small"), (2, 128, 768, "small"), (1, 1408, 256, "small"), (3, 700, 320, "small"),
+    (1, 1409, 256, "128"), (1, 1500, 1088, "128"), (2, 1500, 1152, "128"), (1, 1500, 320, "128"), (1, 1500, 640, "128"),
+    (2, 1500, 192, "staged"),
+])
+def test_cosine_sizes_reach_their_kernel(probe, B, N, D, kernel):
+    """The sizes that the GPU tests take for each kernel's edges run there (on
+    256 compute units, what the host assumes without a GPU)."""
+    assert probe("cosine", B, N, D) == [kernel]
 
 
 def test_k_ranges(direct_loads):

@@ -1,10 +1,10 @@
 """map_decoder_layer on the GPU against the decoder-layer oracle (float64),
 on the same bf16 inputs and weights.
 
-Bar.  The layer stores eight bf16 intermediates (the two RMSNorm outputs, q,
-k and v, the attention output, the block residual, gate and up, their SwiGLU
-product) and its output, each rounded to 2^-9 relative; the products sum
-them in float32.  The layer's update Y - X must match the oracle's in the
+Bar.  The layer stores bf16 intermediates (the two RMSNorm outputs, q, k and
+v, the attention output, the block residual, the SwiGLU product, and gate and
+up where their product runs on the register-staged kernel) and its output, each
+rounded to 2^-9 relative; the products sum them in float32.  The layer's update Y - X must match the oracle's in the
 relative Frobenius norm to 3e-2, and Y itself (dominated by the residual X)
 to 1e-2; the cosine between the updates must exceed 0.999.  Cases: ragged
 packed sequences at a small width (two heads), one sequence of the pruned
@@ -82,9 +82,8 @@ def test_decoder_7b_shape_pruned_length():
 
 def test_decoder_long_sequences_large_tiles():
     """Two sequences of 2944 and 1500 rows at d 1024 (8 heads), SwiGLU 2816:
-    the QKV and gate/up products have enough tiles for the 256 x 256
-    kernel (4444 rows: a ragged last tile row), the output and down
-    products stay on 128 x 128 tiles."""
+    every product runs on tiles of 256 columns, cut into tiles of several
+    heights (4444 rows: a ragged last tile row)."""
     d, H, ff = 1024, 8, 2816
     announce("decoder long sequences, 4444 rows at d 1024")
     rng = np.random.default_rng(8)

@@ -119,9 +119,11 @@ def test_layer1_norms_across_tile_choices(B, N, M):
 
 
 # K in whole slices of 64 but no multiple of 256: an odd count of slices, and
-# even ones on 128 x 128 and 256 x 256 tiles; five slices, and K below four
-# slices (the register-staged kernel)
-@pytest.mark.parametrize("B,N,D", [(1, 1500, 1088), (2, 1500, 1152), (16, 1000, 1152), (3, 700, 320), (2, 1500, 192)])
+# even ones on 128 x 128 and 256 x 256 tiles; five slices on 64 x 64 tiles;
+# K below four slices (the register-staged kernel); five and ten slices on 128 x
+# 128 tiles, whose loop then ends with the last of its five stages
+@pytest.mark.parametrize("B,N,D", [(1, 1500, 1088), (2, 1500, 1152), (16, 1000, 1152), (3, 700, 320), (2, 1500, 192),
+                                   (1, 1500, 320), (1, 1500, 640)])
 def test_cosine_slice_counts(B, N, D):
     from paper_2608_06411_amd import map_similarity
     dev = device()

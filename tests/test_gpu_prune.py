@@ -130,3 +130,15 @@ def test_prune_subset_multiframe_image():
     x = make_inputs(cfg)
     out = _prune(x, cfg.K, cfg.K0, cfg.tau)
     _check(x, out, cfg.K, cfg.K0, cfg.tau, 2e-2)
+
+
+def test_prune_subset_rows_in_global_memory():
+    """A batch whose budget is past what the selection's rows fit in LDS for
+    while the candidate subset still applies: the subset, its second size and
+    the full selection read their coefficient rows from global memory."""
+    from workloads import PredictorShape
+    cfg = get_config("sweep", B=2, N=4000, M=(16, 40), K=320, K0=160, pred=PredictorShape(D=512, D_h=256, d_p=64))
+    announce("prune subset, K = 320 of 4000")
+    x = make_inputs(cfg)
+    out = _prune(x, cfg.K, cfg.K0, cfg.tau)
+    _check(x, out, cfg.K, cfg.K0, cfg.tau, 2e-2)

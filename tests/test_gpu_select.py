@@ -133,10 +133,33 @@ def test_select_r0_candidate_overflow():
 def test_select_rows_in_global_memory(N, K, K0):
     """K past what the own tokens' rows and the pool's fit in LDS for: a last
     workgroup of 1, 32, 33 or 63 tokens, a number of earlier rows that is no
-    multiple of eight, R0 by pool rounds, and a rank that runs out (D < K)."""
+    multiple of eight, R0 by pool rounds, and a rank that runs out (D < K).
+    (64 tokens, all kept, is the largest budget of one workgroup: rows in LDS.)"""
     announce(f"select, rows in global memory N={N} K={K} K0={K0}")
     D = 128 if K > 600 else 512
     V, store = _tokens(N + K0, 1, N, D, "bf16", clusters=N // 2)
     p = peaked_scores(1, N, seed=N + K0)
+    idx, order, gain = _select(store, "bf16", p, K, K0)
+    _check(V, p, K, K0, idx, order, gain)
+
+
+@pytest.mark.parametrize("B,N,K,K0", [(3, 700, 300, 40), (4, 673, 280, 0)])
+def test_select_rows_in_global_memory_batch(B, N, K, K0):
+    """The same for several images: each reads its own rows of the batch."""
+    announce(f"select, rows in global memory B={B} N={N} K={K} K0={K0}")
+    V, store = _tokens(N + B, B, N, 512, "bf16", clusters=N // 2)
+    p = peaked_scores(B, N, seed=N + B)
+    idx, order, gain = _select(store, "bf16", p, K, K0)
+    _check(V, p, K, K0, idx, order, gain)
+
+
+def test_select_update_after_the_picks():
+    """More tokens than workgroups of 64 can own (8192): the own tokens are
+    brought up to date after a round's picks, with pools that end a block of
+    eight rows short and a last workgroup of 9 tokens."""
+    N, K, K0 = 8201, 150, 13
+    announce(f"select, update after the picks N={N} K={K} K0={K0}")
+    V, store = _tokens(N, 1, N, 256, "bf16", clusters=900)
+    p = peaked_scores(1, N, seed=N)
     idx, order, gain = _select(store, "bf16", p, K, K0)
     _check(V, p, K, K0, idx, order, gain)
