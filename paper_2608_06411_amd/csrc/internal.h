@@ -23,9 +23,8 @@ __device__ __forceinline__ float bf16_to_f32(bf16_t b) {
 }
 
 // float -> bf16, round to nearest even (NaN stays NaN, quieted): the hardware
-// conversion, two values per instruction.  Its result equals that of
-// u + 0x7fff + (bit 16 of u), shifted (NaN: the quiet bit set), six
-// instructions a value, on all 2^32 floats.
+// conversion, two values per instruction, against the six instructions a value
+// of u + 0x7fff + (bit 16 of u), shifted, with its test for NaN.
 __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
   return __builtin_bit_cast(bf16_t, static_cast<__bf16>(f));
 }

@@ -224,3 +224,45 @@ def test_decoder_attention_scores_past_float32(lens):
     pos = (place % 400).astype(np.int32)
     got = _run_and_check(X, pos, seq_off, wb, H, "scores past float32")
     assert np.isfinite(got).all()
+
+
+def test_decoder_rounds_to_nearest_even():
+    """The bf16 rounding of float32 sums, read out value by value: one row whose
+    RMSNorm is exactly 1 makes v[j] the sum of three weights that add up to a
+    chosen float32 (its bits in three pieces, every partial sum exact); the row
+    attends to itself only, W_o is the identity and the FFN zero, and the row
+    itself (2^-60) vanishes beside v.  Values: ties on either side of even, the
+    floats beside them, carries into the exponent, both signs, many exponents."""
+    import paper_2608_06411_amd as mp
+    dev = device()
+    d, ff = 2048, 256
+    announce("decoder, rounding to bf16")
+    rng = np.random.default_rng(19)
+    low = np.array([0x0000, 0x0001, 0x7fff, 0x8000, 0x8001, 0xffff, 0x4000, 0xc000], np.uint32)
+    top = rng.integers(0, 0x80, d // 8).astype(np.uint32)
+    top[:4] = [0x7f, 0x7e, 0x00, 0x01]
+    exp = rng.integers(127 - 30, 127 + 30, d // 8).astype(np.uint32)
+    sign = rng.integers(0, 2, d // 8).astype(np.uint32)
+    bits = ((sign << 31) | (exp << 23) | (top << 16))[:, None] | low[None, :]
+    val = bits.reshape(-1).astype(np.uint32).view(np.float32)
+
+    def head(x):  # the leading eight bits, as a float32 that bf16 holds exactly
+        return (x.view(np.uint32) & 0xffff0000).view(np.float32)
+
+    w_v = np.zeros((d, d), np.float32)
+    rest = val.copy()
+    for col in (3, 700, 1900):
+        piece = head(rest)
+        w_v[:, col] = piece
+        rest = rest - piece
+    assert not rest.any()
+    w_qkv = np.concatenate([np.zeros((2 * d, d), np.float32), w_v])
+    wt = {"attn_norm": np.ones(d), "ffn_norm": np.ones(d), "w_qkv": w_qkv, "w_o": np.eye(d), "w_gate_up": np.zeros((2 * ff, d)),
+          "w_down": np.zeros((d, ff))}
+    wt = {k: torch.from_numpy(np.asarray(v, np.float32)).to(dev).to(torch.bfloat16) for k, v in wt.items()}
+    x = torch.full((1, d), 2.0 ** -60, dtype=torch.bfloat16, device=dev)
+    y = mp.map_decoder_layer(mp.DecoderWeights(**wt, n_heads=d // 128, eps=0.0), x, torch.zeros(1, dtype=torch.int32, device=dev),
+                             [0, 1])
+    u = val.view(np.uint32).astype(np.uint64)
+    want = ((u + 0x7fff + ((u >> 16) & 1)) >> 16).astype(np.uint16)  # round to nearest, ties to even
+    np.testing.assert_array_equal(y.view(torch.int16).cpu().numpy().view(np.uint16)[0], want)
