@@ -907,22 +907,26 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
     store_silu<BN / 2, kDmaThreads>(P, bt, m0, n0, L, L, tid);
     return;
   }
-  const bool biased = P.epi == EPI_BIAS_GELU || P.epi == EPI_BIAS;
-  if (P.epi == EPI_COSINE)
+  if (P.epi == EPI_COSINE) {
     cosine_stage(acc, L, rs_tile, rs_tile + BM, lane, wm, wn);
-  else if (biased)
-    stage_bias(P, n0, acc, L, lane, wm, wn);
-  else
-    stage_acc(acc, L, lane, wm, wn);
-  __syncthreads();
-  if (P.epi == EPI_COSINE)
+    __syncthreads();
     cosine_store<kDmaThreads>(P, bt, tm, tn, L, tid);
-  else if (biased)
+  } else if (P.epi == EPI_BIAS_GELU || P.epi == EPI_BIAS) {
+    stage_bias(P, n0, acc, L, lane, wm, wn);
+    __syncthreads();
     store_rows<BN, kDmaThreads, BM, kEpiFinal>(P, bt, m0, n0, L, L, tid);
-  else if (P.epi == EPI_F32)
-    store_rows<BN, kDmaThreads, BM, EPI_F32>(P, bt, m0, n0, L, L, tid);
-  else
-    store_rows<BN, kDmaThreads>(P, bt, m0, n0, L, L, tid);
+  } else {  // (one loop for all of them: the training step's 136 tiles of EPI_F32 and EPI_MUL 10.5 -> 11.5 us, 9.5 so)
+    stage_acc(acc, L, lane, wm, wn);
+    __syncthreads();
+    if (P.epi == EPI_F32)
+      store_rows<BN, kDmaThreads, BM, EPI_F32>(P, bt, m0, n0, L, L, tid);
+    else if (P.epi == EPI_MUL)
+      store_rows<BN, kDmaThreads, BM, EPI_MUL>(P, bt, m0, n0, L, L, tid);
+    else if (P.epi == EPI_RESID)
+      store_rows<BN, kDmaThreads, BM, EPI_RESID>(P, bt, m0, n0, L, L, tid);
+    else
+      store_rows<BN, kDmaThreads, BM, EPI_GELU2>(P, bt, m0, n0, L, L, tid);
+  }
 }
 
 // ------------------------------------------------------------ float32 tiles
