@@ -1425,27 +1425,46 @@ __global__ __launch_bounds__(NT) void select_kernel(const SelectArgs a, int b_be
           const float* ur = U + sk * us;
           const float rk = prr[k];
           const float w0 = Dm[sk * wsd + lane];
-          // all reads first (one LDS round trip), reads and products only
-          // for the groups of 16 rows finished so far
+          // all reads first (one LDS round trip); products only for the groups
+          // of 16 rows finished so far
           float e4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-          auto dot = [&](auto ngc) {
-            constexpr int NG = decltype(ngc)::value;
-            float4 u4[4 * NG], c4[4 * NG];
+          auto add = [&](const float4& u, const float4& c) {
+            e4[0] = fmaf(u.x, c.x, e4[0]); e4[1] = fmaf(u.y, c.y, e4[1]);
+            e4[2] = fmaf(u.z, c.z, e4[2]); e4[3] = fmaf(u.w, c.w, e4[3]);
+          };
+          if constexpr (COLS) {
+            float4 u4[kMaxPool / 4], c4[kMaxPool / 4];
 #pragma unroll
-            for (int j = 0; j < 4 * NG; ++j) {
+            for (int j = 0; j < kMaxPool / 4; ++j) {
               u4[j] = *reinterpret_cast<const float4*>(ur + 4 * j);
               c4[j] = *reinterpret_cast<const float4*>(cr + 4 * j);
             }
 #pragma unroll
-            for (int j = 0; j < 4 * NG; ++j) {
-              e4[0] = fmaf(u4[j].x, c4[j].x, e4[0]); e4[1] = fmaf(u4[j].y, c4[j].y, e4[1]);
-              e4[2] = fmaf(u4[j].z, c4[j].z, e4[2]); e4[3] = fmaf(u4[j].w, c4[j].w, e4[3]);
+            for (int g = 0; g < kMaxPool / 16; ++g) {
+              if (16 * g >= k) break;
+#pragma unroll
+              for (int j = 4 * g; j < 4 * g + 4; ++j) add(u4[j], c4[j]);
             }
-          };
-          if (k > 48) dot(IntC<4>{});
-          else if (k > 32) dot(IntC<3>{});
-          else if (k > 16) dot(IntC<2>{});
-          else if (k > 0) dot(IntC<1>{});
+          } else {
+            // reads of those groups only: other waves read this variant's rows
+            // of C meanwhile (four images at K = 640: 780 -> 757 us; with rows
+            // in LDS it is slower, one image's 160 of 2880 64.9 -> 66.2)
+            auto dot = [&](auto ngc) {
+              constexpr int NG = decltype(ngc)::value;
+              float4 u4[4 * NG], c4[4 * NG];
+#pragma unroll
+              for (int j = 0; j < 4 * NG; ++j) {
+                u4[j] = *reinterpret_cast<const float4*>(ur + 4 * j);
+                c4[j] = *reinterpret_cast<const float4*>(cr + 4 * j);
+              }
+#pragma unroll
+              for (int j = 0; j < 4 * NG; ++j) add(u4[j], c4[j]);
+            };
+            if (k > 48) dot(IntC<4>{});
+            else if (k > 32) dot(IntC<3>{});
+            else if (k > 16) dot(IntC<2>{});
+            else if (k > 0) dot(IntC<1>{});
+          }
           const float v = w0 - ((e4[0] + e4[1]) + (e4[2] + e4[3]));
           const float c = v * rk;  // rk = 1 / r_k, zero when the pick adds no basis vector
           cr[k] = c;
