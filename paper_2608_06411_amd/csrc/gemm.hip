@@ -1776,6 +1776,11 @@ static int gemm_cus() {
 constexpr int kCost256 = 100, kCost192 = 79, kCost128 = 56;
 constexpr int kCostSmall = 43;  // a 128 x 128 tile of the other kernel
 
+// Cost c of a tile over the first problem's K, for a tile over K instead: a
+// tile's start and epilogue take as long as about 800 of K (256 tiles of 256 x
+// 256: 23 us at K = 256, 38 at 1024, 102 at 4096; of 128 x 128: 9, 17, 39).
+static long long cost_at(long long c, int K, const GemmBatch& g) { return c * (K + 800) / (g.p[0].K + 800); }
+
 // Time of `full` tiles of cost c, dispatched first, and `low` tiles of 128
 // rows after them, one tile at a time on each of `cus` units.
 static long long makespan(long long full, long long c, long long low, long long cus) {
@@ -1848,6 +1853,14 @@ static long long plan_big(const GemmBatch& g, GemmBatch& q, int& tm) {
       f = cut < 0 || fewer < 0 ? -1 : fewer / b;
     }
   }
+  // no launch is shorter than its longest tile (the training step's short
+  // products: tiles over 1024 among those over 256, 152 large tiles 22.0 us, 400
+  // of 128 x 128 20.6)
+  for (int i = 0; i < g.count; ++i) {
+    const bool late = i == cut ? best_rows == 0 : !g.p[i].triangular && g.p[i].M <= 128;
+    const long long c = late ? kCost128 : best_tm == 256 ? kCost256 : kCost192;
+    if (g.p[i].K > g.p[0].K) best = std::max(best, cost_at(c, g.p[i].K, g));
+  }
   tm = best_tm;
   // the problem list: full tiles, then tiles of 128 rows and short sums
   q = g;
@@ -1897,7 +1910,10 @@ static long long small_tiles_cost(const GemmBatch& g) {
   }
   const long long cus = gemm_cus(), rounds = (full + cus - 1) / cus, k0 = std::max(1, g.p[0].K);
   const long long left = std::max(0LL, brief - (rounds * cus - full) * (k0 / kb));
-  return rounds * kCostSmall + (left + cus - 1) / cus * (kCostSmall * kb / k0);
+  long long t = rounds * kCostSmall + (left + cus - 1) / cus * (kCostSmall * kb / k0);
+  for (int i = 0; i < g.count; ++i)
+    if (g.p[i].K > g.p[0].K) t = std::max(t, cost_at(kCostSmall, g.p[i].K, g));
+  return t;
 }
 
 static bool big_tiles_pay(const GemmBatch& g, GemmBatch& q, int& tm) {
