@@ -1774,7 +1774,10 @@ static int gemm_cus() {
 
 // Costs of a tile, in hundredths of a 256 x 256 tile over the same K.
 constexpr int kCost256 = 100, kCost192 = 79, kCost128 = 56;
-constexpr int kCostSmall = 43;  // a 128 x 128 tile of the other kernel
+// A 128 x 128 tile of the other kernel; over a short K a second round of them
+// starts while the first one's rows are still on their way out (2 rounds over
+// 256 take 14 to 18 us, one tile 9 to 12; large tiles of 192 rows 19 to 22).
+static int cost_small(int K) { return K < 512 ? 36 : 43; }
 
 // Cost c of a tile over the first problem's K, for a tile over K instead: a
 // tile's start and epilogue take as long as about 800 of K (256 tiles of 256 x
@@ -1908,11 +1911,11 @@ static long long small_tiles_cost(const GemmBatch& g) {
     (late ? brief : full) += n;
     if (late) kb = std::max<long long>(kb, p.K);
   }
-  const long long cus = gemm_cus(), rounds = (full + cus - 1) / cus, k0 = std::max(1, g.p[0].K);
+  const long long cus = gemm_cus(), rounds = (full + cus - 1) / cus, k0 = std::max(1, g.p[0].K), c = cost_small(g.p[0].K);
   const long long left = std::max(0LL, brief - (rounds * cus - full) * (k0 / kb));
-  long long t = rounds * kCostSmall + (left + cus - 1) / cus * (kCostSmall * kb / k0);
+  long long t = rounds * c + (left + cus - 1) / cus * (c * kb / k0);
   for (int i = 0; i < g.count; ++i)
-    if (g.p[i].K > g.p[0].K) t = std::max(t, cost_at(kCostSmall, g.p[i].K, g));
+    if (g.p[i].K > g.p[0].K) t = std::max(t, cost_at(c, g.p[i].K, g));
   return t;
 }
 
