@@ -156,15 +156,20 @@ __device__ __forceinline__ int find_problem(const GemmBatch& args, int tile, int
   return pi;
 }
 
+// Block index -> tile: the launch's classes of tiles (up to first_tiles, up to
+// last_tiles, the rest) one after the other, each XCD-contiguous.
+__device__ __forceinline__ int class_tile(const GemmBatch& args, int b) {
+  const int f = args.first_tiles, h = args.last_tiles;
+  const int lo = b < f ? 0 : b < h ? f : h, hi = b < f ? f : b < h ? h : args.total_tiles;
+  return lo + xcd_remap(b - lo, hi - lo);
+}
+
 // Workgroup -> (problem, batch item, tile row, tile column).
-// The tiles before args.first_tiles run first, each class XCD-contiguous:
-// the launch puts the short tiles into the second class.
 // A problem split over K (ksplit > 1) runs its tiles once per K range kc,
 // the ranges outermost, so that concurrent tiles read the same K columns.
 __device__ __forceinline__ void decode_tile(const GemmBatch& args, int& pi, int& bt, int& tm, int& tn, int& kc,
                                             int& local) {
-  const int b = blockIdx.x, f = args.first_tiles;
-  const int tile = b < f ? xcd_remap(b, f) : f + xcd_remap(b - f, args.total_tiles - f);
+  const int tile = class_tile(args, blockIdx.x);
   pi = find_problem(args, tile, local);
   const GemmProblem& P = args.p[pi];
   bt = local / P.tiles_per_batch;
@@ -1108,8 +1113,7 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(const GemmBatch a
   // rows 0..127, B rows 128..), slot = 0, 1, 2.
   __shared__ uint4 half[9][BM][8];
   __shared__ float rs_big[2 * kBig];  // cosine: 1/norm of the tile's rows, then columns
-  const int f = args.first_tiles, blk = blockIdx.x;
-  const int tile = blk < f ? xcd_remap(blk, f) : f + xcd_remap(blk - f, args.total_tiles - f);
+  const int tile = class_tile(args, blockIdx.x);
   int local;
   const int pi = find_problem(args, tile, local);
   const GemmProblem& P = args.p[pi];
@@ -1683,6 +1687,18 @@ hipError_t launch_gram_reduce(const GemmProblem& partial, float* out, int ldc, c
                        s, partial, out, ldc, rs);
 }
 
+// Compute units of the current device (cached per device).
+static int gemm_cus() {
+  static int cached[16] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 16) return 256;
+  if (cached[dev] == 0) {
+    int c = 0;
+    cached[dev] = hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && c > 0 ? c : 256;
+  }
+  return cached[dev];
+}
+
 // Tiles of `wide` columns over a problem's columns (EPI_SILU: half of a
 // tile's columns are gate columns, the other half their up columns).
 static int col_tiles(const GemmProblem& p, int wide) {
@@ -1703,20 +1719,27 @@ static void count_tiles(GemmBatch& g, int wide) {
     begin += p.tiles_per_batch * p.batch;
   }
   g.total_tiles = begin;
+  g.first_tiles = 0;
+  g.last_tiles = begin;
 }
 
 static void finalize_tiles(GemmBatch& g, int tile) {
   for (int i = 0; i < g.count; ++i) g.p[i].th = tile;
   count_tiles(g, tile);
-  // Two classes of tiles, each spread evenly over the XCDs, the second
-  // dispatched after the first: trailing problems of at most half the first
-  // one's K (the weight folds) come last.  Dealt out with the long ones, 16
-  // short tiles on top of 248 long ones left seven XCDs 33 long tiles for
-  // their 32 compute units, a second wave of workgroups for one tile each
-  // (three 1225-token images: 69 us, now 52).
+  // Classes of tiles, each spread evenly over the XCDs, one dispatched after
+  // the other: trailing problems of at most half the first one's K (the weight
+  // folds) come last.  Dealt out with the long ones, 16 short tiles on top of
+  // 248 long ones left seven XCDs 33 long tiles for their 32 compute units, a
+  // second wave of workgroups for one tile each (three 1225-token images: 69
+  // us, now 52).  A Gram matrix before them, whose tiles take longer over their
+  // epilogue, is a class of its own once the long tiles take more than one
+  // round: with layer 1's in one class some XCDs get nothing but Gram tiles, two
+  // rounds of them (three images of 1339 tokens, D_h = 512, 88.5 us, so 82.3;
+  // in one round, 576 tokens on 64 x 64 tiles 22.0, so 22.3).
   int q = g.count;
   while (q > 1 && 2 * g.p[q - 1].K <= g.p[0].K) --q;
-  g.first_tiles = q < g.count ? g.begin[q] : 0;
+  if (q < g.count) g.last_tiles = g.begin[q];
+  if (q > 1 && g.p[q - 1].epi == EPI_COSINE && g.last_tiles > gemm_cus()) g.first_tiles = g.begin[q - 1];
 }
 
 void gemm_finalize(GemmBatch& g) { finalize_tiles(g, BM); }
@@ -1758,18 +1781,6 @@ bool gemm_direct_loads(map_dtype dt, const GemmBatch& g) {
           k_ranges_ok(p);
   }
   return dma;
-}
-
-// Compute units of the current device (cached per device).
-static int gemm_cus() {
-  static int cached[16] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 16) return 256;
-  if (cached[dev] == 0) {
-    int c = 0;
-    cached[dev] = hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && c > 0 ? c : 256;
-  }
-  return cached[dev];
 }
 
 // Costs of a tile, in hundredths of a 256 x 256 tile over the same K.
@@ -1896,7 +1907,7 @@ static long long plan_big(const GemmBatch& g, GemmBatch& q, int& tm) {
   }
   const int first = q.first_tiles;
   count_tiles(q, kBig);
-  q.first_tiles = first > 0 && first < q.count ? q.begin[first] : 0;
+  if (first > 0 && first < q.count) q.first_tiles = q.begin[first];
   return best;
 }
 

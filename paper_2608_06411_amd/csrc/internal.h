@@ -124,7 +124,8 @@ struct GemmBatch {
   int count;
   int total_tiles;
   int begin[kMaxGemmProblems];  // each problem's first tile
-  int first_tiles;  // tiles dispatched before the rest (0: one class)
+  int first_tiles;              // classes of tiles, dispatched one after the other: up to first_tiles,
+  int last_tiles;               // up to last_tiles, the rest (empty ones are none)
   // bf16 direct-load launches only: norm_blocks more workgroups, dispatched
   // after every tile (on compute units the tiles leave idle), write the row
   // norms of norm_V [norm_rows][norm_D] and their reciprocals, summed in
