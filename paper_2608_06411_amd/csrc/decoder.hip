@@ -16,7 +16,8 @@
 //               key blocks up to the diagonal through LDS on the bf16 matrix
 //               cores with an online softmax; the causal mask follows the
 //               rows' order in their sequence
-//   silu_mul    SiLU(gate) * up, 8 entries per thread
+//   silu_mul    SiLU(gate) * up, 8 entries per thread, where the product did not
+//               form it in its epilogue (weights off a 16-byte boundary)
 #include "internal.h"
 
 namespace mapk {

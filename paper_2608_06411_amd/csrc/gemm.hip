@@ -465,8 +465,8 @@ __device__ __forceinline__ void stage_acc(const f32x16_t (&acc)[2][1], const Sta
 // registers on the way in: its eight waves hold 64 x 32 entries each, so this
 // runs without the addresses and tests of the way out.  (In the loop on the way
 // out one image's layer 1 took 42.2 us against 40.7 so, three of 1225 tokens
-// 52.0 against 50.5.  The 256 x 256 kernel keeps it there: its two passes per
-// half-tile need the smaller code.)
+// 52.0 against 50.5.  The 256 x 256 kernel has it there: each of its four
+// sub-tiles would hold a copy of this code.)
 __device__ __forceinline__ void stage_bias(const GemmProblem& P, int n0, const f32x16_t (&acc)[2][1], const StagedTile& L,
                                            int lane, int wm, int wn) {
   const bf16_t* __restrict__ bias = static_cast<const bf16_t*>(P.bias);
@@ -920,7 +920,7 @@ __global__ __launch_bounds__(kDmaThreads) void gemm_dma_kernel(const GemmBatch a
     stage_bias(P, n0, acc, L, lane, wm, wn);
     __syncthreads();
     store_rows<BN, kDmaThreads, BM, kEpiFinal>(P, bt, m0, n0, L, L, tid);
-  } else {  // (one loop for all of them: the training step's 136 tiles of EPI_F32 and EPI_MUL 10.5 -> 11.5 us, 9.5 so)
+  } else {  // (the training step's 136 tiles of EPI_F32 and EPI_MUL: 11.5 us on one loop for all epilogues, 9.5 so)
     stage_acc(acc, L, lane, wm, wn);
     __syncthreads();
     if (P.epi == EPI_F32)
