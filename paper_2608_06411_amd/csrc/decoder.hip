@@ -125,7 +125,8 @@ __device__ __forceinline__ void dma16(const void* gsrc, uint32_t m) {
 // What bounds it: each block's 32 products of a wave (1024 clocks) and the
 // about as long vector work of its softmax, on two waves per SIMD.  The
 // scores took a trip through LDS and five barriers per block before:
-// 2944 rows, 32 heads: 332 us, now 137; 224 rows: 20 us, now 12.
+// 2944 rows, 32 heads: 332 us, now 140 to 153 (fastest and median of 20); 224
+// rows: 20 us, now 12 to 14.
 constexpr int kKeys = 64;              // keys per block
 constexpr int kKBytes = kKeys * DH * 2;  // one buffer of K, and of V^T
 constexpr float kRescale = 6.0f;       // log2 of the growth that a row's factor may lag behind
